@@ -7,7 +7,9 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <mutex>
 #include <new>
+#include <utility>
 
 #include "internal.h"
 
@@ -20,6 +22,36 @@ bool finite_all(const double *v, size_t n) {
     return true;
 }
 
+// The plan build's temporaries are kept from one build to the next, one block
+// for each device that has plans: a hipMalloc and hipFree of tens of megabytes
+// cost more than the kernels that use them. A build takes the block and
+// gives it back after its stream is synchronised, so builds on several threads
+// and streams never share it (a build that finds it taken allocates its own).
+// It is freed with the device's last plan, when an allocation fails, and when
+// it is above kWorkspaceKeep.
+constexpr int kMaxDevices = 64;
+constexpr size_t kWorkspaceKeep = size_t(512) << 20;
+struct Workspaces {
+    std::mutex m;
+    char *ptr[kMaxDevices] = {};
+    size_t cap[kMaxDevices] = {};
+    int plans[kMaxDevices] = {};
+};
+Workspaces g_workspaces;
+
+// One more plan on the device (change 1) or one less (-1, with that device
+// current): the last one takes the kept block with it.
+void count_plan(int device, int change) {
+    if (device < 0 || device >= kMaxDevices) return;
+    char *p = nullptr;
+    {
+        std::lock_guard<std::mutex> lock(g_workspaces.m);
+        g_workspaces.plans[device] += change;
+        if (g_workspaces.plans[device] <= 0) std::swap(p, g_workspaces.ptr[device]);
+    }
+    if (p) (void)hipFree(p);
+}
+
 bool valid_plan(const bevpool_plan_t *plan) { return plan != nullptr && plan->magic == kPlanMagic; }
 
 void free_plan(bevpool_plan_s *plan) {
@@ -27,24 +59,38 @@ void free_plan(bevpool_plan_s *plan) {
     int prev = -1;
     (void)hipGetDevice(&prev);
     if (prev != plan->device) (void)hipSetDevice(plan->device);
-    (void)hipFree(plan->cell_of_point);
-    (void)hipFree(plan->sorted_point);
-    (void)hipFree(plan->cell_start);
-    (void)hipFree(plan->column_table);
-    (void)hipFree(plan->generic_hdr);
+    (void)hipFree(plan->mem_fixed);
+    (void)hipFree(plan->mem_counted);
     (void)hipFree(plan->generic_runs);
-    (void)hipFree(plan->empty_cells);
-    (void)hipFree(plan->multi_begin);
-    (void)hipFree(plan->multi_cell);
-    (void)hipFree(plan->multi_rows);
-    (void)hipFree(plan->combo_cells);
-    (void)hipFree(plan->combo_cols);
-    (void)hipFree(plan->bwd_mixed);
+    count_plan(plan->device, -1);
     if (prev >= 0 && prev != plan->device) (void)hipSetDevice(prev);
     plan->magic = 0;
     delete plan;
 }
 }  // namespace
+
+// The device's kept block, which the caller then owns (null: none).
+char *bevpool_workspace_out(int dev, size_t *cap) {
+    if (dev < 0 || dev >= kMaxDevices) return nullptr;
+    std::lock_guard<std::mutex> lock(g_workspaces.m);
+    char *p = g_workspaces.ptr[dev];
+    *cap = g_workspaces.cap[dev];
+    g_workspaces.ptr[dev] = nullptr;
+    return p;
+}
+
+// Keeps a block for the device's next build, or frees it (or the smaller one).
+void bevpool_workspace_in(int dev, char *p, size_t cap) {
+    if (!p) return;
+    if (dev >= 0 && dev < kMaxDevices && cap <= kWorkspaceKeep) {
+        std::lock_guard<std::mutex> lock(g_workspaces.m);
+        if (g_workspaces.plans[dev] > 0 && (!g_workspaces.ptr[dev] || g_workspaces.cap[dev] < cap)) {
+            std::swap(g_workspaces.ptr[dev], p);
+            g_workspaces.cap[dev] = cap;
+        }
+    }
+    if (p) (void)hipFree(p);
+}
 
 int bevpool_fail(int code, const char *fmt, ...) {
     va_list ap;
@@ -102,6 +148,7 @@ int make_plan(const double *intrinsics, const double *extrinsics, const int32_t 
         return bevpool_hip_fail(e, "hipGetDevice");
     }
     plan->nz = nz;
+    count_plan(plan->device, 1);
     const int rc = bevpool_build_plan(intrinsics, extrinsics, host_cells, g, nz,
                                       hipStream_t(hip_stream), plan);
     if (rc != BEVPOOL_OK) {

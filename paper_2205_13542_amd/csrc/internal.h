@@ -78,6 +78,9 @@ struct bevpool_plan_s {
     int device;
     bevpool_geometry geom;
     int32_t nz;              // stacked z slabs; cell id (iy * nx + ix) * nz + iz
+    // the arrays below, except generic_runs, lie in two allocations: those
+    // whose sizes the geometry fixes, and those sized by counts of the build
+    char *mem_fixed, *mem_counted;
     int64_t n_points, n_kept;
     int32_t n_cells, n_nonempty, max_per_cell;
     int32_t n_column, n_generic, n_generic_heavy, n_runs, n_empty;
@@ -122,6 +125,11 @@ int bevpool_hip_fail(hipError_t err, const char *what);
 int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
                        const int32_t *host_cells, const bevpool_geometry &g, int32_t nz,
                        hipStream_t stream, bevpool_plan_s *plan);
+// The plan build's temporaries, kept from one build to the next (bevpool.hip):
+// the device's kept block, which the caller then owns, or null; and a block
+// that no queued work uses any more, to be kept or freed.
+char *bevpool_workspace_out(int device, size_t *bytes);
+void bevpool_workspace_in(int device, char *block, size_t bytes);
 int bevpool_launch_backward(const float *G, const void *P, const void *F,
                             const bevpool_plan_s *plan, float *dP, float *dF, int32_t batch,
                             int32_t channels, int32_t dtype, hipStream_t stream);
@@ -131,7 +139,7 @@ int bevpool_launch_to_nchw(const float *in, int64_t in_row_stride, float *out, i
 // temporaries in a fixed device array of kAssocScratchTotal bytes per device.
 constexpr int64_t kAssocMaxPoints = int64_t(1) << 22;
 constexpr int kAssocMaxCams = 16;
-constexpr size_t kAssocScratchTotal = 54529280;   // 52 MiB
+constexpr size_t kAssocScratchTotal = 54529024;   // 52 MiB
 int bevpool_associate_into(const double *intrinsics, const double *extrinsics,
                            const bevpool_geometry &g, int32_t *cell_of_point,
                            int32_t *sorted_point, int32_t *cell_start, hipStream_t stream);

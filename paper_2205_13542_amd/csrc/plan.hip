@@ -6,10 +6,10 @@
 // Kernels, in launch order:
 //   k_project      one thread per point: camera ray -> ego frame -> cell id
 //   k_radix_hist   } stable LSD radix sort of (cell, point id), digits of
-//                  } at most 9 bits;
-//   k_scan...      } input in id order, so ties stay in id order (scans:
-//   k_radix_scatter} one workgroup for a short array, else chunk sums,
-//                    their scan and per-chunk scans from the offsets)
+//                  } at most 9 bits; the first pass reads the cells themselves,
+//   k_scan...      } in id order, so ties stay in id order (scans: one
+//   k_radix_scatter} workgroup for a short array, else chunk sums and
+//                    per-chunk scans from the sums before)
 //   k_cell_start   interval table from the sorted keys
 //   k_cell_stats   non-empty cells and the largest interval
 //   k_combo_walk ... k_generic_runs   work partition of the forward pass:
@@ -50,7 +50,8 @@ constexpr int radix_digit_bits(int bits) {
 constexpr int kScanBlock = 1024;
 constexpr int kScanItems = 4;
 constexpr int kScanChunk = kScanBlock * kScanItems;  // elements per workgroup of a multi-block scan
-constexpr int kScanOneBlockChunks = 8;               // scans of up to 8 chunks take one workgroup
+constexpr int kScanOneBlockChunks = 2;               // scans of up to 2 chunks take one workgroup
+constexpr int kScanBlocks = 1024;                    // workgroups of a multi-block scan, at most
 static_assert(kBlock == 256, "a sort tile is four waves of 512 keys");
 
 constexpr int kArgCams = 16;   // cameras whose calibration travels in the kernel arguments
@@ -60,62 +61,57 @@ struct ProjectArgs {
     const double *extr;  // [N][12]
     double cal[kArgCams * 16];   // [N][4] intrinsics, then [N][12] extrinsics (intr null)
     bevpool_geometry g;
-    FastDiv div_w, div_h, div_d;
-    int32_t n_points, n_cells, nz;
+    FastDiv div_w, div_h, div_b;   // div_b: blocks of kProjectBins depth bins
+    int32_t n_threads, n_blocks, nz;
     int32_t *cell_of_point;
-    uint32_t *keys;
-    int32_t *vals;
 };
+constexpr int kProjectBins = 4;
 
 // Sec. III-B, first paragraph: the pixel's ray at depth bin d, in the ego
 // frame, quantised at the cell size, z like x and y; points outside the grid
 // or the nz stacked z slabs are dropped. Cell id (iy * nx + ix) * nz + iz.
-// Sort key = cell id, or n_cells for a dropped point (last).
+// One thread per pixel and kProjectBins depth bins, whose points share the
+// pixel's two quotients: the fp64 divisions are what the kernel spends its time
+// on, five for each point otherwise, here three (16.0 -> 12.6 us for 2 M points,
+// with the sort's keys and ids no longer written here).
 __global__ __launch_bounds__(kBlock) void k_project(ProjectArgs a) {
-    const int32_t p = blockIdx.x * kBlock + threadIdx.x;
-    if (p >= a.n_points) return;
+    const int32_t x = blockIdx.x * kBlock + threadIdx.x;
+    if (x >= a.n_threads) return;
     const bevpool_geometry &g = a.g;
-    const uint32_t q_w = fdiv(uint32_t(p), a.div_w);
-    const int w = p - int(q_w) * g.feat_w;
+    const uint32_t q_w = fdiv(uint32_t(x), a.div_w);
+    const int w = x - int(q_w) * g.feat_w;
     const uint32_t q_h = fdiv(q_w, a.div_h);
     const int h = int(q_w) - int(q_h) * g.feat_h;
-    const int n = int(fdiv(q_h, a.div_d));
-    const int d = int(q_h) - n * g.n_depth;
+    const int n = int(fdiv(q_h, a.div_b));
+    const int d0 = (int(q_h) - n * a.n_blocks) * kProjectBins;
 
     const double *I = a.intr ? a.intr + 4 * n : a.cal + 4 * n;
     const double *E = a.intr ? a.extr + 12 * n : a.cal + 4 * g.n_cams + 12 * n;
     const double fx = I[0], fy = I[1], cx = I[2], cy = I[3];
-    const double depth = g.depth_min + double(d) * g.depth_step;
     const double u = double(w) + g.pixel_offset;
     const double v = double(h) + g.pixel_offset;
-    const double xc = depth * ((u - cx) / fx);
-    const double yc = depth * ((v - cy) / fy);
-    const double zc = depth;
-    const double X = ((E[0] * xc + E[1] * yc) + E[2] * zc) + E[3];
-    const double Y = ((E[4] * xc + E[5] * yc) + E[6] * zc) + E[7];
-    const double Z = ((E[8] * xc + E[9] * yc) + E[10] * zc) + E[11];
-    const double qx = floor((X - g.x_min) / g.cell_x);
-    const double qy = floor((Y - g.y_min) / g.cell_y);
-    const double qz = floor((Z - g.z_min) / g.z_cell);
-    int32_t cell = -1;
-    if (qx >= 0.0 && qx < double(g.nx) && qy >= 0.0 && qy < double(g.ny) && qz >= 0.0 &&
-        qz < double(a.nz))
-        cell = (int32_t(qy) * g.nx + int32_t(qx)) * a.nz + int32_t(qz);
-    a.cell_of_point[p] = cell;
-    a.keys[p] = cell >= 0 ? uint32_t(cell) : uint32_t(a.n_cells);
-    a.vals[p] = p;
-}
-
-// A stored association (bevpool_plan_import): the sort keys and point ids
-// from a cell map validated on the host.
-__global__ __launch_bounds__(kBlock) void k_keys_from_cells(const int32_t *cell_of_point,
-                                                            int32_t n_points, int32_t n_cells,
-                                                            uint32_t *keys, int32_t *vals) {
-    const int32_t p = blockIdx.x * kBlock + threadIdx.x;
-    if (p >= n_points) return;
-    const int32_t cell = cell_of_point[p];
-    keys[p] = cell >= 0 ? uint32_t(cell) : uint32_t(n_cells);
-    vals[p] = p;
+    const double ru = (u - cx) / fx;
+    const double rv = (v - cy) / fy;
+#pragma unroll
+    for (int k = 0; k < kProjectBins; ++k) {
+        const int d = d0 + k;
+        if (d >= g.n_depth) break;
+        const double depth = g.depth_min + double(d) * g.depth_step;
+        const double xc = depth * ru;
+        const double yc = depth * rv;
+        const double zc = depth;
+        const double X = ((E[0] * xc + E[1] * yc) + E[2] * zc) + E[3];
+        const double Y = ((E[4] * xc + E[5] * yc) + E[6] * zc) + E[7];
+        const double Z = ((E[8] * xc + E[9] * yc) + E[10] * zc) + E[11];
+        const double qx = floor((X - g.x_min) / g.cell_x);
+        const double qy = floor((Y - g.y_min) / g.cell_y);
+        const double qz = floor((Z - g.z_min) / g.z_cell);
+        int32_t cell = -1;
+        if (qx >= 0.0 && qx < double(g.nx) && qy >= 0.0 && qy < double(g.ny) && qz >= 0.0 &&
+            qz < double(a.nz))
+            cell = (int32_t(qy) * g.nx + int32_t(qx)) * a.nz + int32_t(qz);
+        a.cell_of_point[((int64_t(n) * g.n_depth + d) * g.feat_h + h) * g.feat_w + w] = cell;
+    }
 }
 
 // ---------------------------------------------------------------- scan
@@ -169,52 +165,88 @@ __global__ __launch_bounds__(kScanBlock) void k_scan(int32_t *data, int64_t n, i
         }
         carry += blocksum;
     }
-    if (threadIdx.x == 0) *total = carry;
+    if (threadIdx.x == 0 && total) *total = carry;
 }
 
-// Multi-block exclusive scan, for arrays longer than one chunk: each
-// workgroup sums its chunk, one workgroup scans the chunk sums (k_scan),
-// and each workgroup scans its chunk again from its offset.
-__global__ __launch_bounds__(kScanBlock) void k_scan_sums(const int32_t *data, int64_t n,
-                                                          int32_t *sums) {
+// Multi-block exclusive scan, for arrays longer than a few chunks: each
+// workgroup sums its chunks, then each adds up the sums before its own (few,
+// and in cache) and scans its chunks from there. Up to kScanJobs arrays are
+// scanned by one pair of launches (grid y): the three scans of a classification
+// took nine launches, each 2 to 5 us.
+constexpr int kScanJobs = 3;
+struct ScanJob {
+    int32_t *data;
+    int64_t n;
+    int32_t *total;     // receives the sum; may be null
+    int32_t *sums;      // kScanBlocks ints
+    int32_t blocks;     // workgroups
+    int32_t chunks;     // chunks of each
+};
+struct ScanArgs {
+    ScanJob job[kScanJobs];
+};
+
+__global__ __launch_bounds__(kScanBlock) void k_scan_sums(ScanArgs args) {
     __shared__ int lds[kScanBlock / kWaveSize];
-    const int64_t i0 = int64_t(blockIdx.x) * kScanChunk + int64_t(threadIdx.x) * kScanItems;
+    const ScanJob a = args.job[blockIdx.y];
+    if (int(blockIdx.x) >= a.blocks) return;
     int local = 0;
+    for (int c = 0; c < a.chunks; ++c) {
+        const int64_t i0 = (int64_t(blockIdx.x) * a.chunks + c) * kScanChunk + int64_t(threadIdx.x) * kScanItems;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) local += (i0 + k < n) ? data[i0 + k] : 0;
+        for (int k = 0; k < kScanItems; ++k) local += (i0 + k < a.n) ? a.data[i0 + k] : 0;
+    }
     int total;
     (void)block_exclusive_scan<kScanBlock>(local, lds, &total);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+    if (threadIdx.x == 0) a.sums[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_scan_apply(int32_t *data, int64_t n,
-                                                           const int32_t *offsets) {
+__global__ __launch_bounds__(kScanBlock) void k_scan_apply(ScanArgs args) {
     __shared__ int lds[kScanBlock / kWaveSize];
-    const int64_t i0 = int64_t(blockIdx.x) * kScanChunk + int64_t(threadIdx.x) * kScanItems;
-    int v[kScanItems];
-    int local = 0;
+    const ScanJob a = args.job[blockIdx.y];
+    if (int(blockIdx.x) >= a.blocks) return;
+    static_assert(kScanBlocks <= kScanBlock, "a thread per sum");
+    int carry;
+    (void)block_exclusive_scan<kScanBlock>(threadIdx.x < blockIdx.x ? a.sums[threadIdx.x] : 0, lds, &carry);
+    for (int c = 0; c < a.chunks; ++c) {
+        const int64_t i0 = (int64_t(blockIdx.x) * a.chunks + c) * kScanChunk + int64_t(threadIdx.x) * kScanItems;
+        int v[kScanItems];
+        int local = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = (i0 + k < n) ? data[i0 + k] : 0;
-        local += v[k];
-    }
-    int total;
-    int run = offsets[blockIdx.x] + block_exclusive_scan<kScanBlock>(local, lds, &total);
+        for (int k = 0; k < kScanItems; ++k) {
+            v[k] = (i0 + k < a.n) ? a.data[i0 + k] : 0;
+            local += v[k];
+        }
+        int total;
+        int run = carry + block_exclusive_scan<kScanBlock>(local, lds, &total);
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        if (i0 + k < n) data[i0 + k] = run;
-        run += v[k];
+        for (int k = 0; k < kScanItems; ++k) {
+            if (i0 + k < a.n) a.data[i0 + k] = run;
+            run += v[k];
+        }
+        carry += total;
     }
+    if (a.total && threadIdx.x == 0 && int(blockIdx.x) == a.blocks - 1) *a.total = carry;
 }
 
 // ---------------------------------------------------------------- radix sort
 
-// Digit histogram of each 2048-key tile, stored digit-major:
+// Digit histogram of each tile, stored digit-major:
 // hist[digit * n_tiles + tile], so an exclusive scan of the whole array
 // gives every (digit, tile) its first output slot in stable order.
 // Digit counts of one tile: hist[digit * tiles + tile], digits of dbits
 // bits (dbits <= kRadixBits) from bit `shift` on.
-__global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *keys, int32_t n,
+// With CELLS the keys are the points' cells as projected (the sort's first
+// pass): a dropped point's -1 counts as n_cells, which comes last, and the
+// values are the positions themselves, so neither is written beforehand.
+template <bool CELLS>
+__device__ __forceinline__ uint32_t sort_key(const uint32_t *keys, int64_t i, int32_t n_cells) {
+    const uint32_t k = keys[i];
+    return CELLS ? min(k, uint32_t(n_cells)) : k;
+}
+
+template <bool CELLS>
+__global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *keys, int32_t n, int32_t n_cells,
                                                        int shift, int dbits, int32_t *hist) {
     __shared__ int cnt[kRadixBins];
     const int bins = 1 << dbits;
@@ -225,22 +257,23 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *keys, int
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
         const int64_t i = base + int64_t(k) * kBlock + threadIdx.x;
-        if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & mask], 1);
+        if (i < n) atomicAdd(&cnt[(sort_key<CELLS>(keys, i, n_cells) >> shift) & mask], 1);
     }
     __syncthreads();
     for (int d = threadIdx.x; d < bins; d += kBlock)
         hist[int64_t(d) * gridDim.x + blockIdx.x] = cnt[d];
 }
 
-// Stable scatter. Wave w of a tile owns keys [w*512, (w+1)*512) of the tile
+// Stable scatter. Wave w of a tile owns keys [w, w + 1) * kWaveItems of the tile
 // and walks them 64 at a time in order. Within a step, a key's rank among
 // equal digits comes from one ballot per digit bit: lanes whose ballots
 // agree on every bit hold the same digit. A per-wave LDS counter per
 // digit carries ranks across steps. Per-wave counts are then prefixed across
 // the waves and added to the scanned global offsets.
+template <bool CELLS>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *keys_in,
                                                           const int32_t *vals_in, int32_t n,
-                                                          int shift, int dbits,
+                                                          int32_t n_cells, int shift, int dbits,
                                                           const int32_t *hist_scan,
                                                           uint32_t *keys_out, int32_t *vals_out) {
     __shared__ int wcount[kWaves][kRadixBins];
@@ -265,8 +298,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *keys_i
     for (int k = 0; k < kSortItems; ++k) {
         const int64_t i = base + int64_t(k) * kWaveSize + lane;
         const bool valid = i < n;
-        key[k] = valid ? keys_in[i] : 0u;
-        val[k] = valid ? vals_in[i] : 0;
+        key[k] = valid ? sort_key<CELLS>(keys_in, i, n_cells) : 0u;
+        val[k] = CELLS ? int32_t(i) : valid ? vals_in[i] : 0;
         const uint32_t digit = (key[k] >> shift) & mask;
         uint64_t same = __ballot(valid);
 #pragma unroll
@@ -314,21 +347,67 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *keys_i
 // Sorted keys are the kept cells, then n_cells for every dropped point. Slot
 // i (0..n) fills the cells in (key[i-1], key[i]] with i; each entry of
 // cell_start is written by exactly one slot.
+// A thread takes kStartItems slots, whose keys it reads as one piece (skeys is
+// 16-byte aligned). Runs of more than kStartRun empty cells (rows of the grid
+// that no camera sees) are filled by the whole wave: by one thread they were
+// what the kernel waited for (9.1 us of a nuScenes-shaped build, now 4.0).
+constexpr int kStartItems = 4;
+constexpr int kStartRun = 16;
 __global__ __launch_bounds__(kBlock) void k_cell_start(const uint32_t *skeys, int32_t n,
                                                        int32_t n_cells, int32_t *cell_start) {
-    const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (i > n) return;
-    const int64_t prev = (i == 0) ? -1 : int64_t(skeys[i - 1]);
-    const int64_t cur = (i == n) ? int64_t(n_cells) : int64_t(skeys[i]);
-    for (int64_t c = prev + 1; c <= cur; ++c) cell_start[c] = int32_t(i);
+    const int64_t i0 = (int64_t(blockIdx.x) * kBlock + threadIdx.x) * kStartItems;
+    uint32_t key[kStartItems];
+    if (i0 + kStartItems <= n) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(skeys + i0);
+        key[0] = v.x;
+        key[1] = v.y;
+        key[2] = v.z;
+        key[3] = v.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kStartItems; ++k) key[k] = i0 + k < n ? skeys[i0 + k] : uint32_t(n_cells);
+    }
+    int32_t prev = i0 == 0 ? -1 : i0 <= n ? int32_t(skeys[i0 - 1]) : n_cells;
+    // long runs of empty cells (whole rows of the grid) are filled by the wave
+    const int lane = threadIdx.x & (kWaveSize - 1);
+#pragma unroll
+    for (int k = 0; k < kStartItems; ++k) {
+        const bool in = i0 + k <= n;
+        const int32_t last = in ? int32_t(key[k]) : prev;
+        const bool wide = last - prev > kStartRun;
+        if (!wide)
+            for (int32_t c = prev + 1; c <= last; ++c) cell_start[c] = int32_t(i0 + k);
+        for (uint64_t rest = __ballot(wide); rest != 0; rest &= rest - 1) {
+            const int from = __builtin_ctzll(rest);
+            const int32_t hi = __shfl(last, from), v = __shfl(int32_t(i0 + k), from);
+            for (int32_t c = __shfl(prev, from) + 1 + lane; c <= hi; c += kWaveSize) cell_start[c] = v;
+        }
+        prev = last;
+    }
 }
 
 // Counters shared by the whole grid (counts, maxima) are reduced in the
 // workgroup first and updated by one atomic per workgroup, and the kernels
 // that update them run a capped grid over their elements: atomics on one
-// address are performed one after another, so one per wave (what the
-// compiler makes of per-thread updates) would cost tens of microseconds.
+// address are performed one after another, about 11 ns each, so one per wave
+// (what the compiler makes of per-thread updates) would cost tens of
+// microseconds. Each counter is kept in kShards words on cache lines of their
+// own, which workgroups update in turn; the host adds them up (or takes the
+// largest).
 constexpr int kReduceBlocks = 256;
+constexpr int kShards = 8;
+constexpr int kCounters = 16;      // counters of a shard: 64 bytes
+
+__device__ __forceinline__ int32_t *shard(int32_t *counters, int id) {
+    return counters + (blockIdx.x % kShards) * kCounters + id;
+}
+
+// Counters [first, first + 2) of every shard to zero (2 * kShards threads).
+__device__ __forceinline__ void clear_pair(int32_t *counters, int first, int t) {
+    if (t < 2 * kShards) counters[t / 2 * kCounters + first + t % 2] = 0;
+}
+
+__global__ void k_clear_pair(int32_t *counters, int first) { clear_pair(counters, first, int(threadIdx.x)); }
 
 // Workgroup sum (MAX: maximum) of one value per thread; every thread of the
 // workgroup calls it, the result is valid in thread 0. s_red holds kWaves
@@ -349,11 +428,11 @@ __device__ __forceinline__ int32_t block_reduce(int32_t v, int32_t *s_red) {
     return v;
 }
 
-// Non-empty cells and the largest interval into stats[0..1], the kept
-// count (cell_start[n_cells]) into stats[10]; clears two per-cell arrays
+// Non-empty cells and the largest interval into counters 0 and 1, the kept
+// count (cell_start[n_cells]) into counter 10; clears two per-cell arrays
 // (the combo walk's counters) on the way.
 __global__ __launch_bounds__(kBlock) void k_cell_stats(const int32_t *cell_start, int32_t n_cells,
-                                                       int32_t *stats /* nonempty, max */,
+                                                       int32_t *stats,
                                                        int32_t *clear_a, int32_t *clear_b) {
     __shared__ int32_t s_n[kWaves], s_m[kWaves];
     if (blockIdx.x == 0 && threadIdx.x == 0) stats[10] = cell_start[n_cells];
@@ -368,8 +447,8 @@ __global__ __launch_bounds__(kBlock) void k_cell_stats(const int32_t *cell_start
     nonempty = block_reduce<false>(nonempty, s_n);
     most = block_reduce<true>(most, s_m);
     if (threadIdx.x == 0) {
-        if (nonempty > 0) atomicAdd(&stats[0], nonempty);
-        if (most > 0) atomicMax(&stats[1], most);
+        if (nonempty > 0) atomicAdd(shard(stats, 0), nonempty);
+        if (most > 0) atomicMax(shard(stats, 1), most);
     }
 }
 
@@ -396,9 +475,8 @@ struct ComboArgs {
     int32_t planes;             // segments a combo may have and stay column-served
     int32_t *seg_cell;          // [planes][N*D*W]: cell of segment s of the combo, or -1
     int32_t *seg_range;         // [planes][N*D*W]: its rows h_lo | h_hi << 16
-    int32_t *max_seg;           // most segments of a column-served combo
-    int32_t *served_pts;        // kept points of column-served combos
-    int32_t *class_counters;    // [2]: k_cell_class's counters, cleared here for it
+    int32_t *counters;          // 6: most segments of a column-served combo, 7: kept points of such
+                                // combos; 4 and 5, k_cell_class's, are cleared here for it
 };
 
 // One thread per combo walks its H rows and splits the kept ones into
@@ -479,7 +557,7 @@ __device__ __forceinline__ void combo_walk_one(const ComboArgs &a, int32_t X, in
 
 __global__ __launch_bounds__(kBlock) void k_combo_walk(ComboArgs a) {
     __shared__ int32_t s_m[kWaves], s_p[kWaves];
-    if (blockIdx.x == 0 && threadIdx.x < 2) a.class_counters[threadIdx.x] = 0;
+    if (blockIdx.x == 0) clear_pair(a.counters, 4, int(threadIdx.x));
     const int64_t n_combo = int64_t(a.N) * a.D * a.W;
     int32_t max_seg = 0, served_pts = 0;
     for (int64_t x = int64_t(blockIdx.x) * kBlock + threadIdx.x; x < n_combo;
@@ -488,17 +566,17 @@ __global__ __launch_bounds__(kBlock) void k_combo_walk(ComboArgs a) {
     max_seg = block_reduce<true>(max_seg, s_m);
     served_pts = block_reduce<false>(served_pts, s_p);
     if (threadIdx.x == 0) {
-        if (max_seg > 0) atomicMax(a.max_seg, max_seg);
-        if (served_pts > 0) atomicAdd(a.served_pts, served_pts);
+        if (max_seg > 0) atomicMax(shard(a.counters, 6), max_seg);
+        if (served_pts > 0) atomicAdd(shard(a.counters, 7), served_pts);
     }
 }
 
 // Per cell: generic flag, empty flag (both arrays n_cells + 1 long, the
-// last entry 0); counters[0] += column-served cells, counters[1] += heavy
+// last entry 0); counter 4 += column-served cells, counter 5 += heavy
 // generic cells.
 __global__ __launch_bounds__(kBlock) void k_cell_class(ComboArgs a, const int32_t *cell_start,
                                                        int32_t n_cells, int32_t *generic_flag,
-                                                       int32_t *empty_flag, int32_t *counters) {
+                                                       int32_t *empty_flag) {
     __shared__ int32_t s_s[kWaves], s_h[kWaves];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         generic_flag[n_cells] = 0;   // the flags are scanned over n_cells + 1 entries
@@ -516,8 +594,8 @@ __global__ __launch_bounds__(kBlock) void k_cell_class(ComboArgs a, const int32_
     n_served = block_reduce<false>(n_served, s_s);
     n_heavy = block_reduce<false>(n_heavy, s_h);
     if (threadIdx.x == 0) {
-        if (n_served > 0) atomicAdd(&counters[0], n_served);
-        if (n_heavy > 0) atomicAdd(&counters[1], n_heavy);
+        if (n_served > 0) atomicAdd(shard(a.counters, 4), n_served);
+        if (n_heavy > 0) atomicAdd(shard(a.counters, 5), n_heavy);
     }
 }
 
@@ -547,16 +625,16 @@ __global__ __launch_bounds__(kBlock) void k_clear_table(int2 *table, int64_t n) 
     if (t < n) table[t] = make_int2(-1, 0);
 }
 
-// Planes in use: one past the highest plane of the column table that holds
-// an entry.
+// Planes in use (counter 2): one past the highest plane of the column table
+// that holds an entry.
 __global__ __launch_bounds__(kBlock) void k_planes_used(const int2 *table, int64_t n,
-                                                        int32_t n_combo, int32_t *planes) {
+                                                        int32_t n_combo, int32_t *counters) {
     __shared__ int32_t s_m[kWaves];
     int32_t most = 0;
     for (int64_t t = int64_t(blockIdx.x) * kBlock + threadIdx.x; t < n; t += int64_t(gridDim.x) * kBlock)
         if (table[t].x >= 0) most = max(most, int32_t(t / n_combo) + 1);
     most = block_reduce<true>(most, s_m);
-    if (threadIdx.x == 0 && most > 0) atomicMax(planes, most);
+    if (threadIdx.x == 0 && most > 0) atomicMax(shard(counters, 2), most);
 }
 
 // Clean combos by pixel column: entry (n, w, d) = {cell, rows} of combo
@@ -578,11 +656,11 @@ __global__ __launch_bounds__(kBlock) void k_combo_cols(const int32_t *combo_cell
 // Backward blocks (kBwdBlockCols pixel columns of one camera) that hold a
 // combo that is not clean: flagged 1 (every writer stores the same value).
 // One workgroup per backward block (camera n, kBwdBlockCols pixel columns):
-// flags[block] = 1 when one of its combos is not clean, and *count adds the
-// flagged blocks.
+// flags[block] = 1 when one of its combos is not clean, and counter 12 adds
+// the flagged blocks.
 __global__ __launch_bounds__(kBlock) void k_bwd_blocks(const int32_t *combo_cell, int32_t W,
                                                        int32_t D, int32_t blocks_w, int32_t *flags,
-                                                       int32_t *count) {
+                                                       int32_t *counters) {
     __shared__ int32_t s_m[kWaves];
     const int32_t n = blockIdx.x / blocks_w, w0 = (blockIdx.x % blocks_w) * kBwdBlockCols;
     int32_t mixed = 0;
@@ -593,7 +671,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_blocks(const int32_t *combo_cell
     mixed = block_reduce<true>(mixed, s_m);
     if (threadIdx.x == 0) {
         flags[blockIdx.x] = mixed;
-        if (mixed) atomicAdd(count, 1);
+        if (mixed) atomicAdd(shard(counters, 12), 1);
     }
 }
 
@@ -601,7 +679,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_blocks(const int32_t *combo_cell
 // combos become generic.
 __global__ __launch_bounds__(kBlock) void k_demote_multi(ComboArgs a, int32_t n_cells) {
     const int32_t c = blockIdx.x * kBlock + threadIdx.x;
-    if (c < 2) a.class_counters[c] = 0;
+    clear_pair(a.counters, 4, c);
     if (c < n_cells && a.cell_generic[c] == 0 && a.cell_ncombo[c] > 1) a.cell_generic[c] = 1;
 }
 
@@ -653,12 +731,13 @@ __global__ __launch_bounds__(kBlock) void k_multi_cells(const uint32_t *key, con
 
 // The borrowed rows of the first kCombineInline slots of each multi-combo
 // cell, next to each other, so that the combine kernel finds them with one
-// access; -1 past the cell's last slot. One thread per entry.
-__global__ __launch_bounds__(kBlock) void k_multi_rows(const int32_t *multi_begin, int32_t n_multi,
+// access; -1 past the cell's last slot. One thread per entry, launched for the
+// most cells there can be (their number stays on the device until the end).
+__global__ __launch_bounds__(kBlock) void k_multi_rows(const int32_t *multi_begin, const int32_t *n_multi,
                                                        const int32_t *empty_cells,
                                                        int32_t *multi_rows) {
     const int64_t x = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (x >= int64_t(n_multi) * kCombineInline) return;
+    if (x >= int64_t(*n_multi) * kCombineInline) return;
     const int32_t k = int32_t(x / kCombineInline), u = int32_t(x % kCombineInline);
     const int32_t s = multi_begin[k] + u;
     multi_rows[x] = s < multi_begin[k + 1] ? empty_cells[s] : -1;
@@ -748,7 +827,18 @@ int reduce_blocks(int64_t n) { return std::max(1, std::min(blocks_for(n), kReduc
 template <typename T>
 int dev_alloc(T **p, size_t count, const char *what) {
     *p = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(p), (count ? count : 1) * sizeof(T));
+    const size_t bytes = (count ? count : 1) * sizeof(T);
+    hipError_t e = hipMalloc(reinterpret_cast<void **>(p), bytes);
+    if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
+        int dev = -1;
+        size_t cap = 0;
+        char *kept = hipGetDevice(&dev) == hipSuccess ? bevpool_workspace_out(dev, &cap) : nullptr;
+        if (kept) {
+            (void)hipGetLastError();
+            (void)hipFree(kept);
+            e = hipMalloc(reinterpret_cast<void **>(p), bytes);
+        }
+    }
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
         (void)hipGetLastError();
         return bevpool_fail(BEVPOOL_ERR_OOM, "out of device memory allocating %s (%zu bytes)", what,
@@ -758,11 +848,11 @@ int dev_alloc(T **p, size_t count, const char *what) {
     return BEVPOOL_OK;
 }
 
-// One device allocation carved into the plan build's temporaries: each
-// piece is rounded to 256 bytes, and the total is reserved from upper bounds
-// that the geometry fixes, so a build makes one allocation for them instead
-// of one per array (each hipMalloc and hipFree costs about 10 us of host
-// time).
+// One device allocation carved into arrays: each piece is rounded to 256
+// bytes, and the total is reserved beforehand, so that a plan build makes one
+// allocation for its temporaries (from upper bounds that the geometry fixes)
+// and two or three for the plan, instead of one per array (each hipMalloc
+// and hipFree costs about 10 us of host time).
 struct Arena {
     char *base = nullptr;
     size_t cap = 0, used = 0;
@@ -772,8 +862,7 @@ struct Arena {
         const size_t b = piece(count * sizeof(T));
         if (used + b > cap) {
             *p = nullptr;
-            return bevpool_fail(BEVPOOL_ERR_HIP, "plan temporaries: %s does not fit the reserved %zu bytes",
-                                what, cap);
+            return bevpool_fail(BEVPOOL_ERR_HIP, "plan arrays: %s does not fit the reserved %zu bytes", what, cap);
         }
         *p = reinterpret_cast<T *>(base + used);
         used += b;
@@ -781,20 +870,85 @@ struct Arena {
     }
 };
 
-// Chunk sums a multi-block scan of n elements needs.
-int64_t scan_sums_needed(int64_t n) { return (n + kScanChunk - 1) / kScanChunk; }
+// Exclusive scans in place of up to kScanJobs arrays, in one pair of launches
+// (or one launch where a single short array is left to one workgroup).
+struct Scan {
+    int32_t *data;
+    int64_t n;
+    int32_t *total;   // receives the sum; may be null
+};
+constexpr int64_t kScanSums = int64_t(kScanJobs) * kScanBlocks;   // scratch ints
 
-// Exclusive scan of data[0..n) in place; *total receives the sum. sums:
-// scratch of scan_sums_needed(n) ints (unused for a single chunk).
-void device_scan(int32_t *data, int64_t n, int32_t *total, int32_t *sums, hipStream_t stream) {
-    const int64_t nb = scan_sums_needed(n);
-    if (nb <= kScanOneBlockChunks) {   // one launch: the workgroup walks the chunks
-        hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanBlock), 0, stream, data, n, total);
+template <int N>
+void device_scan(const Scan (&scans)[N], int32_t *sums, hipStream_t stream) {
+    static_assert(N <= kScanJobs, "jobs of one launch");
+    if (N == 1 && scans[0].n <= int64_t(kScanOneBlockChunks) * kScanChunk) {
+        hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanBlock), 0, stream, scans[0].data, scans[0].n, scans[0].total);
         return;
     }
-    hipLaunchKernelGGL(k_scan_sums, dim3(uint32_t(nb)), dim3(kScanBlock), 0, stream, data, n, sums);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanBlock), 0, stream, sums, nb, total);
-    hipLaunchKernelGGL(k_scan_apply, dim3(uint32_t(nb)), dim3(kScanBlock), 0, stream, data, n, sums);
+    ScanArgs a = {};
+    int blocks = 1;
+    for (int i = 0; i < N; ++i) {
+        const int64_t chunks = std::max<int64_t>(1, (scans[i].n + kScanChunk - 1) / kScanChunk);
+        ScanJob &b = a.job[i];
+        b.data = scans[i].data;
+        b.n = scans[i].n;
+        b.total = scans[i].total;
+        b.sums = sums + i * kScanBlocks;
+        b.chunks = int32_t((chunks + kScanBlocks - 1) / kScanBlocks);
+        b.blocks = int32_t((chunks + b.chunks - 1) / b.chunks);
+        blocks = std::max(blocks, b.blocks);
+    }
+    hipLaunchKernelGGL(k_scan_sums, dim3(blocks, N), dim3(kScanBlock), 0, stream, a);
+    hipLaunchKernelGGL(k_scan_apply, dim3(blocks, N), dim3(kScanBlock), 0, stream, a);
+}
+
+void device_scan(int32_t *data, int64_t n, int32_t *total, int32_t *sums, hipStream_t stream) {
+    const Scan one[1] = {{data, n, total}};
+    device_scan(one, sums, stream);
+}
+
+// Stable LSD radix sort of n (key, value) pairs on the keys' low `bits` bits
+// (radix_passes passes of radix_digit_bits bits), ping-ponging between keys /
+// kalt and vals / valt; keys and vals are left pointing at the buffers that
+// hold the result. With cells, the first pass takes the points' cells as keys
+// and their positions as values, and writes to keys and valt.
+int radix_sort(const int32_t *cells, int32_t n_cells, uint32_t *&keys, uint32_t *kalt, int32_t *&vals, int32_t *valt,
+               int32_t n, int bits, int32_t *hist, int32_t *sums, hipStream_t stream) {
+    if (n <= 0) return BEVPOOL_OK;
+    const int tiles = int((int64_t(n) + kSortTile - 1) / kSortTile);
+    const int passes = radix_passes(bits), dbits = radix_digit_bits(bits);
+    uint32_t *kin = keys, *kout = kalt;
+    int32_t *vin = vals, *vout = valt;
+    if (cells) std::swap(kin, kout);
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = dbits * pass;
+        const bool first = cells && pass == 0;
+        const uint32_t *src = first ? reinterpret_cast<const uint32_t *>(cells) : kin;
+        if (first) hipLaunchKernelGGL(k_radix_hist<true>, dim3(tiles), dim3(kBlock), 0, stream, src, n, n_cells, shift, dbits, hist);
+        else hipLaunchKernelGGL(k_radix_hist<false>, dim3(tiles), dim3(kBlock), 0, stream, src, n, n_cells, shift, dbits, hist);
+        device_scan(hist, int64_t(tiles) << dbits, nullptr, sums, stream);
+        if (first) hipLaunchKernelGGL(k_radix_scatter<true>, dim3(tiles), dim3(kBlock), 0, stream, src, vin, n, n_cells, shift, dbits, hist, kout, vout);
+        else hipLaunchKernelGGL(k_radix_scatter<false>, dim3(tiles), dim3(kBlock), 0, stream, src, vin, n, n_cells, shift, dbits, hist, kout, vout);
+        BEVPOOL_HIP(hipGetLastError());
+        std::swap(kin, kout);
+        std::swap(vin, vout);
+    }
+    keys = kin;
+    vals = vin;
+    return BEVPOOL_OK;
+}
+
+// Projection arguments common to both entry points.
+void project_args(ProjectArgs &pa, const bevpool_geometry &g, int32_t nz, int32_t *cell_of_point) {
+    pa.g = g;
+    pa.n_blocks = (g.n_depth + kProjectBins - 1) / kProjectBins;
+    pa.div_w = make_fastdiv(uint32_t(g.feat_w));
+    pa.div_h = make_fastdiv(uint32_t(g.feat_h));
+    pa.div_b = make_fastdiv(uint32_t(pa.n_blocks));
+    pa.n_threads = g.n_cams * pa.n_blocks * g.feat_h * g.feat_w;   // at most the points
+    pa.nz = nz;
+    pa.cell_of_point = cell_of_point;
 }
 
 }  // namespace
@@ -820,13 +974,27 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     plan->n_cells = n_cells;
     plan->nz = nz;
 
-    int rc;
-    if ((rc = dev_alloc(&plan->cell_of_point, size_t(np), "cell_of_point"))) return rc;
-    if ((rc = dev_alloc(&plan->sorted_point, size_t(np), "sorted_point"))) return rc;
-    if ((rc = dev_alloc(&plan->cell_start, size_t(n_cells) + 1, "cell_start"))) return rc;
-    if ((rc = dev_alloc(&plan->column_table, size_t(n_seg), "column_table"))) return rc;
+    const int32_t bwd_bw = (W + kBwdBlockCols - 1) / kBwdBlockCols;
+    plan->n_bwd_blocks = N * bwd_bw;
 
-    // temporaries, carved from one arena that is freed on every exit path below
+    // the plan's arrays whose sizes the geometry fixes (the combo cells and
+    // columns serve the backward pass)
+    int rc;
+    Arena fixed;
+    fixed.cap = 2 * Arena::piece(size_t(np) * 4) + Arena::piece((size_t(n_cells) + 1) * 4) +
+                Arena::piece(size_t(n_seg) * 8) + Arena::piece(size_t(n_combo) * 4) +
+                Arena::piece(size_t(n_combo) * 8) + Arena::piece(size_t(plan->n_bwd_blocks) * 4);
+    if ((rc = dev_alloc(&fixed.base, fixed.cap, "the plan"))) return rc;
+    plan->mem_fixed = fixed.base;
+    if ((rc = fixed.take(&plan->cell_of_point, size_t(np), "cell_of_point"))) return rc;
+    if ((rc = fixed.take(&plan->sorted_point, size_t(np), "sorted_point"))) return rc;
+    if ((rc = fixed.take(&plan->cell_start, size_t(n_cells) + 1, "cell_start"))) return rc;
+    if ((rc = fixed.take(&plan->column_table, size_t(n_seg), "column_table"))) return rc;
+    if ((rc = fixed.take(&plan->combo_cells, size_t(n_combo), "combo cells"))) return rc;
+    if ((rc = fixed.take(&plan->combo_cols, size_t(n_combo), "combos by column"))) return rc;
+    if ((rc = fixed.take(&plan->bwd_mixed, size_t(plan->n_bwd_blocks), "backward blocks"))) return rc;
+
+    // temporaries, carved from one arena that is given back on every exit path below
     const int64_t sort_cap = np64 > n_cells ? np64 : int64_t(n_cells);
     const int sort_tiles_cap = int((sort_cap + kSortTile - 1) / kSortTile);
     Arena arena;
@@ -838,35 +1006,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     int32_t *combo_cell = nullptr, *combo_range = nullptr, *combo_flag = nullptr;
     int32_t *cell_generic = nullptr, *cell_ncombo = nullptr, *head_scan = nullptr;
     int32_t *run_scan = nullptr, *run_begin = nullptr, *pos_of_cell = nullptr;
-    auto cleanup = [&]() { (void)hipFree(arena.base); };
 
-    // Stable LSD radix sort of n (key, value) pairs on the keys' low `bits`
-    // bits (radix_passes passes of radix_digit_bits bits), ping-ponging
-    // between keys / kalt and vals / valt; keys and vals are left pointing at
-    // the buffers that hold the result (vals ends in valt after an odd number
-    // of passes).
-    auto radix_sort = [&](uint32_t *&keys, uint32_t *kalt, int32_t *&vals, int32_t *valt, int32_t n,
-                          int bits) -> int {
-        if (n <= 0) return BEVPOOL_OK;
-        const int tiles = int((int64_t(n) + kSortTile - 1) / kSortTile);
-        const int passes = radix_passes(bits), dbits = radix_digit_bits(bits);
-        uint32_t *kin = keys, *kout = kalt;
-        int32_t *vin = vals, *vout = valt;
-        for (int pass = 0; pass < passes; ++pass) {
-            const int shift = dbits * pass;
-            hipLaunchKernelGGL(k_radix_hist, dim3(tiles), dim3(kBlock), 0, stream, kin, n, shift,
-                               dbits, hist);
-            device_scan(hist, int64_t(tiles) << dbits, small + 3, scan_sums, stream);
-            hipLaunchKernelGGL(k_radix_scatter, dim3(tiles), dim3(kBlock), 0, stream, kin, vin, n,
-                               shift, dbits, hist, kout, vout);
-            BEVPOOL_HIP(hipGetLastError());
-            std::swap(kin, kout);
-            std::swap(vin, vout);
-        }
-        keys = kin;
-        vals = vin;
-        return BEVPOOL_OK;
-    };
     auto bits_for = [](int64_t max_key) {
         int b = 1;
         while ((int64_t(1) << b) <= max_key) ++b;
@@ -875,8 +1015,20 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     auto fill = [&](int32_t *p, int64_t n, int32_t v) {
         if (n > 0) hipLaunchKernelGGL(k_fill, dim3(blocks_for(n)), dim3(kBlock), 0, stream, p, n, v);
     };
-    auto to_host = [&](int32_t *dst, const int32_t *src) -> int {
-        BEVPOOL_HIP(hipMemcpyAsync(dst, src, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+    // the counters, read back and joined over their shards (maxima: 1, 2, 6;
+    // the others are sums, or kept in one shard only); waits for the stream
+    int32_t h[kCounters];
+    auto read_counters = [&]() -> int {
+        int32_t all[kShards * kCounters];
+        BEVPOOL_HIP(hipMemcpyAsync(all, small, sizeof(all), hipMemcpyDeviceToHost, stream));
+        BEVPOOL_HIP(hipStreamSynchronize(stream));
+        for (int i = 0; i < kCounters; ++i) {
+            h[i] = all[i];
+            for (int u = 1; u < kShards; ++u) {
+                const int32_t v = all[u * kCounters + i];
+                h[i] = (i == 1 || i == 2 || i == 6) ? std::max(h[i], v) : h[i] + v;
+            }
+        }
         return BEVPOOL_OK;
     };
 
@@ -891,15 +1043,21 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
             const size_t cells1_b = Arena::piece((size_t(n_cells) + 1) * i4);
             const size_t combo1_b = Arena::piece((size_t(n_seg) + 1) * i4);
             arena.cap = Arena::piece(size_t(g.n_cams) * 16 * sizeof(double)) + 4 * sort_b +
-                        Arena::piece(size_t(sort_tiles_cap) * kRadixBins * i4) + Arena::piece(16 * i4) +
-                        Arena::piece(size_t(scan_sums_needed(sort_cap + 1)) * i4) +
+                        Arena::piece(size_t(sort_tiles_cap) * kRadixBins * i4) +
+                        Arena::piece(size_t(kShards) * kCounters * i4) + Arena::piece(size_t(kScanSums) * i4) +
                         5 * cells1_b +                 // flag_a, flag_b, cell_generic, cell_ncombo, run_begin
                         Arena::piece(size_t(n_cells) * i4) +          // pos_of_cell
                         2 * combo1_b +                 // combo_flag, head_scan
                         Arena::piece(size_t(n_combo) * i4) +          // combo_range
                         2 * Arena::piece(size_t(n_seg) * i4) +        // seg_cell, seg_range
                         Arena::piece((size_t(np) + 1) * i4);          // run_scan
-            if ((rc2 = dev_alloc(&arena.base, arena.cap, "plan temporaries"))) return rc2;
+            const size_t need = arena.cap;
+            arena.base = bevpool_workspace_out(plan->device, &arena.cap);
+            if (!arena.base || arena.cap < need) {
+                (void)hipFree(arena.base);
+                arena.cap = need;
+                if ((rc2 = dev_alloc(&arena.base, need, "plan temporaries"))) return rc2;
+            }
         }
         const bool cal_in_args = g.n_cams <= kArgCams;
         if (!host_cells && !cal_in_args &&
@@ -910,30 +1068,21 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         if ((rc2 = arena.take(&vals_a, size_t(sort_cap), "sort values"))) return rc2;
         if ((rc2 = arena.take(&vals_b, size_t(sort_cap), "sort values"))) return rc2;
         if ((rc2 = arena.take(&hist, size_t(sort_tiles_cap) * kRadixBins, "radix histogram"))) return rc2;
-        // [0..1] cell stats, [3] scan totals, [4..5] class counters, [6] most
-        // segments of a combo, [7] their kept points, [8] generic cells, [9]
-        // empty cells, [10] kept points, [11] segments of multi-combo cells,
-        // [12] backward blocks with a combo that is not clean
-        if ((rc2 = arena.take(&small, 16, "plan counters"))) return rc2;
-        // the longest scan is over sort_cap + 1 elements (radix histograms
-        // are shorter)
-        if ((rc2 = arena.take(&scan_sums, size_t(scan_sums_needed(sort_cap + 1)), "scan chunk sums")))
-            return rc2;
+        // kShards shards of counters: [0..1] cell stats, [2] planes in use, [3]
+        // multi-combo cells, [4..5] class counters, [6] most segments of a
+        // combo, [7] their kept points, [8] generic cells, [9] empty cells,
+        // [10] kept points, [11] segments of multi-combo cells, [12] backward
+        // blocks with a combo that is not clean, [13] gather runs
+        if ((rc2 = arena.take(&small, size_t(kShards) * kCounters, "plan counters"))) return rc2;
+        if ((rc2 = arena.take(&scan_sums, size_t(kScanSums), "scan chunk sums"))) return rc2;
         if ((rc2 = arena.take(&flag_a, size_t(n_cells) + 1, "flags"))) return rc2;
         if ((rc2 = arena.take(&flag_b, size_t(n_cells) + 1, "flags"))) return rc2;
 
-        fill(small, 16, 0);
-        // the sort's point ids start in the buffer from which its passes end
-        // in sorted_point (vals_b for an odd number of passes)
-        const bool odd_passes = radix_passes(bits_for(n_cells)) % 2 == 1;
-        int32_t *ids0 = odd_passes ? vals_b : plan->sorted_point;
-        int32_t *ids1 = odd_passes ? plan->sorted_point : vals_b;
+        fill(small, kShards * kCounters, 0);
         if (host_cells) {
             // a stored association: the cell map as exported, checked by the caller
             BEVPOOL_HIP(hipMemcpyAsync(plan->cell_of_point, host_cells, sizeof(int32_t) * size_t(np),
                                        hipMemcpyHostToDevice, stream));
-            hipLaunchKernelGGL(k_keys_from_cells, dim3(blocks_for(np)), dim3(kBlock), 0, stream,
-                               plan->cell_of_point, np, n_cells, keys_a, ids0);
         } else {
             ProjectArgs pa;
             if (cal_in_args) {
@@ -953,26 +1102,20 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
 
             // Sec. III-B, precomputation: cell of every point, then the points
             // sorted by (cell, id) and the interval table.
-            pa.g = g;
-            pa.div_w = make_fastdiv(uint32_t(W));
-            pa.div_h = make_fastdiv(uint32_t(H));
-            pa.div_d = make_fastdiv(uint32_t(D));
-            pa.n_points = np;
-            pa.n_cells = n_cells;
-            pa.nz = nz;
-            pa.cell_of_point = plan->cell_of_point;
-            pa.keys = keys_a;
-            pa.vals = ids0;
-            hipLaunchKernelGGL(k_project, dim3(blocks_for(np)), dim3(kBlock), 0, stream, pa);
+            project_args(pa, g, nz, plan->cell_of_point);
+            hipLaunchKernelGGL(k_project, dim3(blocks_for(pa.n_threads)), dim3(kBlock), 0, stream, pa);
         }
         BEVPOOL_HIP(hipGetLastError());
+        // the passes alternate between two value buffers and end in
+        // sorted_point: the first writes to it when their number is odd
+        const int cell_bits = bits_for(n_cells);
+        const bool odd_passes = radix_passes(cell_bits) % 2 == 1;
         uint32_t *skeys = keys_a;
-        int32_t *sids = ids0;
-        if ((rc2 = radix_sort(skeys, keys_b, sids, ids1, np, bits_for(n_cells)))) return rc2;
-        if (sids != plan->sorted_point)
-            BEVPOOL_HIP(hipMemcpyAsync(plan->sorted_point, sids, sizeof(int32_t) * size_t(np),
-                                       hipMemcpyDeviceToDevice, stream));
-        hipLaunchKernelGGL(k_cell_start, dim3(blocks_for(int64_t(np) + 1)), dim3(kBlock), 0,
+        int32_t *sids = odd_passes ? vals_b : plan->sorted_point;
+        if ((rc2 = radix_sort(plan->cell_of_point, n_cells, skeys, keys_b, sids,
+                              odd_passes ? plan->sorted_point : vals_b, np, cell_bits, hist, scan_sums, stream)))
+            return rc2;
+        hipLaunchKernelGGL(k_cell_start, dim3(blocks_for(int64_t(np) / kStartItems + 1)), dim3(kBlock), 0,
                            stream, skeys, np, n_cells, plan->cell_start);
         // per-cell counters of the combo walk, cleared by k_cell_stats
         if ((rc2 = arena.take(&cell_generic, size_t(n_cells), "cell classes"))) return rc2;
@@ -982,9 +1125,6 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         BEVPOOL_HIP(hipGetLastError());
 
         // combos, cell classes and the column table
-        // the combo cells and rows stay with the plan (the backward pass
-        // reads them)
-        if ((rc2 = dev_alloc(&plan->combo_cells, size_t(n_combo), "combo cells"))) return rc2;
         combo_cell = plan->combo_cells;
         if ((rc2 = arena.take(&combo_range, size_t(n_combo), "combo ranges"))) return rc2;
         if ((rc2 = arena.take(&combo_flag, size_t(n_seg) + 1, "segment flags"))) return rc2;
@@ -1005,26 +1145,24 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         ca.planes = planes;
         ca.seg_cell = seg_cell;
         ca.seg_range = seg_range;
-        ca.max_seg = small + 6;
-        ca.served_pts = small + 7;
-        ca.class_counters = small + 4;
+        ca.counters = small;
         // (k_combo_table writes every entry of every plane: no clearing first)
         hipLaunchKernelGGL(k_combo_walk, dim3(reduce_blocks(n_combo)), dim3(kBlock), 0, stream, ca);
         int32_t stats[4], counters[2], n_gen = 0, n_empty = 0, kept = 0, n_part = 0;
-        // (the class counters small[4..5] are cleared by k_combo_walk or
+        // (the class counters 4 and 5 are cleared by k_combo_walk or
         // k_demote_multi, which run before each classification)
         auto classify = [&]() -> int {
             hipLaunchKernelGGL(k_cell_class, dim3(reduce_blocks(n_cells)), dim3(kBlock), 0, stream, ca,
-                               plan->cell_start, n_cells, flag_a, flag_b, small + 4);
+                               plan->cell_start, n_cells, flag_a, flag_b);
             hipLaunchKernelGGL(k_combo_table, dim3(blocks_for(n_seg_act)), dim3(kBlock), 0, stream,
                                ca, plan->column_table, combo_flag);
-            device_scan(flag_a, int64_t(n_cells) + 1, small + 8, scan_sums, stream);       // generic cells
-            device_scan(flag_b, int64_t(n_cells) + 1, small + 9, scan_sums, stream);       // empty cells
-            device_scan(combo_flag, n_seg_act + 1, small + 11, scan_sums, stream);  // segments of multi cells
+            const Scan scans[3] = {{flag_a, int64_t(n_cells) + 1, small + 8},      // generic cells
+                                   {flag_b, int64_t(n_cells) + 1, small + 9},      // empty cells
+                                   {combo_flag, n_seg_act + 1, small + 11}};       // segments of multi cells
+            device_scan(scans, scan_sums, stream);
             BEVPOOL_HIP(hipGetLastError());
-            int32_t h[12];
-            BEVPOOL_HIP(hipMemcpyAsync(h, small, sizeof(h), hipMemcpyDeviceToHost, stream));
-            BEVPOOL_HIP(hipStreamSynchronize(stream));
+            int rc3;
+            if ((rc3 = read_counters())) return rc3;
             stats[0] = h[0];
             stats[1] = h[1];
             stats[2] = h[6];       // most segments of a column-served combo
@@ -1048,7 +1186,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
                                plan->column_table, n_seg);
             fill(cell_generic, n_cells, 0);
             fill(cell_ncombo, n_cells, 0);
-            fill(small + 6, 2, 0);
+            hipLaunchKernelGGL(k_clear_pair, dim3(1), dim3(2 * kShards), 0, stream, small, 6);
             hipLaunchKernelGGL(k_combo_walk, dim3(reduce_blocks(n_combo)), dim3(kBlock), 0, stream, ca);
             if ((rc2 = classify())) return rc2;
         }
@@ -1068,24 +1206,32 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         // planes in use, from the final table (cells demoted to generic leave
         // their segments' planes empty)
         hipLaunchKernelGGL(k_planes_used, dim3(reduce_blocks(n_seg_act)), dim3(kBlock), 0, stream,
-                           plan->column_table, n_seg_act, int32_t(n_combo), small + 2);
+                           plan->column_table, n_seg_act, int32_t(n_combo), small);
 
         // the backward blocks holding a combo that is not clean, and the clean
         // combos of the other blocks by pixel column
-        const int32_t bwd_bw = (W + kBwdBlockCols - 1) / kBwdBlockCols;
-        plan->n_bwd_blocks = N * bwd_bw;
-        if ((rc2 = dev_alloc(&plan->bwd_mixed, size_t(plan->n_bwd_blocks), "backward blocks")))
-            return rc2;
         hipLaunchKernelGGL(k_bwd_blocks, dim3(plan->n_bwd_blocks), dim3(kBlock), 0, stream,
-                           combo_cell, W, D, bwd_bw, plan->bwd_mixed, small + 12);
-        if ((rc2 = dev_alloc(&plan->combo_cols, size_t(n_combo), "combos by column"))) return rc2;
+                           combo_cell, W, D, bwd_bw, plan->bwd_mixed, small);
         hipLaunchKernelGGL(k_combo_cols, dim3(blocks_for(n_combo)), dim3(kBlock), 0, stream,
                            combo_cell, combo_range, plan->bwd_mixed, int32_t(n_combo), W, D, bwd_bw,
                            plan->combo_cols);
         BEVPOOL_HIP(hipGetLastError());
 
         // cells without points, ascending
-        if ((rc2 = dev_alloc(&plan->empty_cells, size_t(n_empty), "empty_cells"))) return rc2;
+        // (with them the other arrays that the counts size; a multi-combo cell
+        // has two slots or more)
+        const int32_t multi_cap = n_part / 2;
+        Arena counted;
+        counted.cap = Arena::piece(size_t(n_empty) * 4) + Arena::piece((size_t(multi_cap) + 1) * 4) +
+                      Arena::piece(size_t(multi_cap) * 4) + Arena::piece(size_t(multi_cap) * kCombineInline * 4) +
+                      Arena::piece(size_t(n_gen) * 16);
+        if ((rc2 = dev_alloc(&counted.base, counted.cap, "the plan"))) return rc2;
+        plan->mem_counted = counted.base;
+        if ((rc2 = counted.take(&plan->empty_cells, size_t(n_empty), "empty_cells"))) return rc2;
+        if ((rc2 = counted.take(&plan->multi_begin, size_t(multi_cap) + 1, "multi_begin"))) return rc2;
+        if ((rc2 = counted.take(&plan->multi_cell, size_t(multi_cap), "multi_cell"))) return rc2;
+        if ((rc2 = counted.take(&plan->multi_rows, size_t(multi_cap) * kCombineInline, "multi_rows"))) return rc2;
+        if ((rc2 = counted.take(&plan->generic_hdr, size_t(n_gen), "generic_hdr"))) return rc2;
         hipLaunchKernelGGL(k_empty_list, dim3(blocks_for(n_cells)), dim3(kBlock), 0, stream, flag_b,
                            n_cells, plan->empty_cells);
 
@@ -1097,52 +1243,48 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         if (n_part > 0) {
             hipLaunchKernelGGL(k_multi_compact, dim3(blocks_for(n_seg_act)), dim3(kBlock), 0, stream,
                                seg_cell, combo_flag, int32_t(n_seg_act), keys_a, vals_a);
-            if ((rc2 = radix_sort(mkeys, keys_b, mvals, vals_b, n_part, bits_for(n_cells)))) return rc2;
+            if ((rc2 = radix_sort(nullptr, 0, mkeys, keys_b, mvals, vals_b, n_part, cell_bits, hist, scan_sums, stream)))
+                return rc2;
             hipLaunchKernelGGL(k_multi_slots, dim3(blocks_for(n_part)), dim3(kBlock), 0, stream,
                                mkeys, mvals, n_part, plan->empty_cells, plan->column_table,
                                head_scan);
-            // the number of multi-combo cells lands in small[3]
+            // the number of multi-combo cells lands in counter 3
             device_scan(head_scan, int64_t(n_part) + 1, small + 3, scan_sums, stream);
         } else {
             fill(head_scan, 1, 0);
         }
         BEVPOOL_HIP(hipGetLastError());
-        // one read-back for the counts that size the remaining arrays
-        int32_t h[16];
-        BEVPOOL_HIP(hipMemcpyAsync(h, small, sizeof(h), hipMemcpyDeviceToHost, stream));
-        BEVPOOL_HIP(hipStreamSynchronize(stream));
-        const int32_t n_multi = n_part > 0 ? h[3] : 0;
-        plan->n_bwd_mixed = h[12];
-        plan->n_multi = n_multi;
-        plan->n_planes = h[2] > 0 ? h[2] : 1;
-        if ((rc2 = dev_alloc(&plan->multi_begin, size_t(n_multi) + 1, "multi_begin"))) return rc2;
-        if ((rc2 = dev_alloc(&plan->multi_cell, size_t(n_multi), "multi_cell"))) return rc2;
-        if ((rc2 = dev_alloc(&plan->multi_rows, size_t(n_multi) * kCombineInline, "multi_rows")))
-            return rc2;
-        if ((rc2 = dev_alloc(&plan->generic_hdr, size_t(n_gen), "generic_hdr"))) return rc2;
         hipLaunchKernelGGL(k_multi_cells, dim3(blocks_for(int64_t(n_part) + 1)), dim3(kBlock), 0,
                            stream, mkeys, head_scan, n_part, plan->multi_begin, plan->multi_cell);
-        if (n_multi > 0)
-            hipLaunchKernelGGL(k_multi_rows, dim3(blocks_for(int64_t(n_multi) * kCombineInline)),
-                               dim3(kBlock), 0, stream, plan->multi_begin, n_multi,
+        if (multi_cap > 0)
+            hipLaunchKernelGGL(k_multi_rows, dim3(blocks_for(int64_t(multi_cap) * kCombineInline)),
+                               dim3(kBlock), 0, stream, plan->multi_begin, small + 3,
                                plan->empty_cells, plan->multi_rows);
         BEVPOOL_HIP(hipGetLastError());
+        // (counter 3 is 0 without slots: no scan has written it)
+        auto read_rest = [&]() -> int {
+            int rc3;
+            if ((rc3 = read_counters())) return rc3;
+            plan->n_bwd_mixed = h[12];
+            plan->n_multi = h[3];
+            plan->n_planes = h[2] > 0 ? h[2] : 1;
+            plan->n_runs = h[13];
+            return BEVPOOL_OK;
+        };
 
         // generic cells by descending point count
         if (n_gen == 0) {
             // every cell with points is column-served (a level rig): no runs
-            plan->n_runs = 0;
-            if ((rc2 = dev_alloc(&plan->generic_runs, 0, "generic_runs"))) return rc2;
-            BEVPOOL_HIP(hipGetLastError());
-            BEVPOOL_HIP(hipStreamSynchronize(stream));
-            return BEVPOOL_OK;
+            // (generic_runs stays null: a resource of no bytes)
+            return read_rest();
         }
         uint32_t *gen_key = keys_a;   // the sort buffers are free again after k_multi_cells
         int32_t *gen_cell = vals_a;
         hipLaunchKernelGGL(k_compact_generic, dim3(blocks_for(n_cells)), dim3(kBlock), 0, stream,
                            plan->cell_start, n_cells, flag_a, plan->max_per_cell, gen_key, gen_cell);
         BEVPOOL_HIP(hipGetLastError());
-        if ((rc2 = radix_sort(gen_key, keys_b, gen_cell, vals_b, n_gen, bits_for(plan->max_per_cell))))
+        if ((rc2 = radix_sort(nullptr, 0, gen_key, keys_b, gen_cell, vals_b, n_gen, bits_for(plan->max_per_cell), hist,
+                              scan_sums, stream)))
             return rc2;
 
         // runs of the generic cells, in list order
@@ -1154,20 +1296,17 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
             hipLaunchKernelGGL(k_run_flags, dim3(blocks_for(kept)), dim3(kBlock), 0, stream,
                                plan->sorted_point, kept, plan->cell_of_point, flag_a, HW, div_hw,
                                div_d, D, run_scan);
-        device_scan(run_scan, int64_t(kept) + 1, small + 3, scan_sums, stream);
+        device_scan(run_scan, int64_t(kept) + 1, nullptr, scan_sums, stream);
         if (n_gen > 0)
             hipLaunchKernelGGL(k_generic_counts, dim3(blocks_for(n_gen)), dim3(kBlock), 0, stream,
                                gen_cell, n_gen, plan->cell_start, run_scan, run_begin, pos_of_cell);
-        device_scan(run_begin, int64_t(n_gen) + 1, small + 3, scan_sums, stream);
+        device_scan(run_begin, int64_t(n_gen) + 1, small + 13, scan_sums, stream);
         if (n_gen > 0)
             hipLaunchKernelGGL(k_generic_hdr, dim3(blocks_for(n_gen)), dim3(kBlock), 0, stream,
                                gen_cell, n_gen, plan->cell_start, run_begin, plan->generic_hdr);
         BEVPOOL_HIP(hipGetLastError());
-        int32_t n_runs;
-        if ((rc2 = to_host(&n_runs, run_begin + n_gen))) return rc2;
-        BEVPOOL_HIP(hipStreamSynchronize(stream));
-        plan->n_runs = n_runs;
-        if ((rc2 = dev_alloc(&plan->generic_runs, size_t(n_runs), "generic_runs"))) return rc2;
+        if ((rc2 = read_rest())) return rc2;
+        if ((rc2 = dev_alloc(&plan->generic_runs, size_t(plan->n_runs), "generic_runs"))) return rc2;
         if (kept > 0)
             hipLaunchKernelGGL(k_generic_runs, dim3(blocks_for(kept)), dim3(kBlock), 0, stream,
                                plan->sorted_point, kept, plan->cell_of_point, plan->cell_start,
@@ -1179,7 +1318,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     };
     rc = run();
     if (rc != BEVPOOL_OK) (void)hipStreamSynchronize(stream);
-    cleanup();
+    bevpool_workspace_in(plan->device, arena.base, arena.cap);
     return rc;
 }
 
@@ -1188,8 +1327,8 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
 // bevpool_associate_noalloc: the association of the "Precomputation"
 // paragraph (every point's cell, the points sorted by cell, the interval
 // table) into caller buffers, for callers that cannot allocate. Its
-// temporaries (the calibration, the radix sort's second key and value
-// arrays, histograms, counters, scan sums) live in one file-scope device
+// temporaries (the calibration, the radix sort's key arrays and second value
+// array, histograms, scan sums) live in one file-scope device
 // array of fixed size, which each device holds while the library is loaded.
 // Host code never uses the array's name as an address: the device address
 // comes from hipGetSymbolAddress, once per device, with that device current.
@@ -1199,13 +1338,13 @@ namespace {
 constexpr size_t scratch_piece(size_t b) { return (b + 255) & ~size_t(255); }
 constexpr int64_t kAssocTiles = (kAssocMaxPoints + kSortTile - 1) / kSortTile;
 constexpr int64_t kAssocSums = (kAssocTiles * kRadixBins + kScanChunk - 1) / kScanChunk;
+static_assert(kAssocSums <= kScanBlocks, "one chunk a workgroup");
 constexpr size_t kOffCalib = 0;
 constexpr size_t kOffKeysA = kOffCalib + scratch_piece(size_t(kAssocMaxCams) * 16 * sizeof(double));
 constexpr size_t kOffKeysB = kOffKeysA + scratch_piece(size_t(kAssocMaxPoints) * 4);
 constexpr size_t kOffValsB = kOffKeysB + scratch_piece(size_t(kAssocMaxPoints) * 4);
 constexpr size_t kOffHist = kOffValsB + scratch_piece(size_t(kAssocMaxPoints) * 4);
-constexpr size_t kOffSmall = kOffHist + scratch_piece(size_t(kAssocTiles) * kRadixBins * 4);
-constexpr size_t kOffSums = kOffSmall + scratch_piece(16 * 4);
+constexpr size_t kOffSums = kOffHist + scratch_piece(size_t(kAssocTiles) * kRadixBins * 4);
 constexpr size_t kAssocScratchBytes = kOffSums + scratch_piece(size_t(kAssocSums) * 4);
 static_assert(kAssocScratchBytes == kAssocScratchTotal, "scratch size stated in internal.h");
 
@@ -1264,7 +1403,6 @@ int bevpool_associate_into(const double *intrinsics, const double *extrinsics,
     uint32_t *keys_b = reinterpret_cast<uint32_t *>(base + kOffKeysB);
     int32_t *vals_b = reinterpret_cast<int32_t *>(base + kOffValsB);
     int32_t *hist = reinterpret_cast<int32_t *>(base + kOffHist);
-    int32_t *small = reinterpret_cast<int32_t *>(base + kOffSmall);
     int32_t *sums = reinterpret_cast<int32_t *>(base + kOffSums);
     const int32_t np = int32_t(np64), n_cells = g.nx * g.ny;
 
@@ -1273,49 +1411,24 @@ int bevpool_associate_into(const double *intrinsics, const double *extrinsics,
     for (int i = 0; i < 4 * g.n_cams; ++i) ca.v[i] = intrinsics[i];
     for (int i = 0; i < 12 * g.n_cams; ++i) ca.v[4 * g.n_cams + i] = extrinsics[i];
     hipLaunchKernelGGL(k_store_calib, dim3(1), dim3(kBlock), 0, stream, ca, calib);
-    // counters start at zero on every call (the array keeps the last call's contents)
-    hipLaunchKernelGGL(k_fill, dim3(1), dim3(kBlock), 0, stream, small, int64_t(16), 0);
 
     ProjectArgs pa;
     pa.intr = calib;
     pa.extr = calib + 4 * g.n_cams;
-    pa.g = g;
-    pa.div_w = make_fastdiv(uint32_t(g.feat_w));
-    pa.div_h = make_fastdiv(uint32_t(g.feat_h));
-    pa.div_d = make_fastdiv(uint32_t(g.n_depth));
-    pa.n_points = np;
-    pa.n_cells = n_cells;
-    pa.nz = 1;
-    // stable LSD radix sort of (cell, point id) on the cell's bits
-    // (radix_passes passes); the ids start in the buffer from which the
-    // passes end in sorted_point
+    project_args(pa, g, 1, cell_of_point);
+    hipLaunchKernelGGL(k_project, dim3(blocks_for(pa.n_threads)), dim3(kBlock), 0, stream, pa);
+    BEVPOOL_HIP(hipGetLastError());
+    // stable LSD radix sort of (cell, point id) on the cell's bits; the passes
+    // end in sorted_point
     int bits = 1;
     while ((int64_t(1) << bits) <= int64_t(n_cells)) ++bits;
     const bool odd_passes = radix_passes(bits) % 2 == 1;
-    pa.cell_of_point = cell_of_point;
-    pa.keys = keys_a;
-    pa.vals = odd_passes ? vals_b : sorted_point;
-    hipLaunchKernelGGL(k_project, dim3(blocks_for(np)), dim3(kBlock), 0, stream, pa);
-    BEVPOOL_HIP(hipGetLastError());
-
-    const int tiles = int((int64_t(np) + kSortTile - 1) / kSortTile);
-    uint32_t *kin = keys_a, *kout = keys_b;
-    int32_t *vin = pa.vals, *vout = odd_passes ? sorted_point : vals_b;
-    const int dbits = radix_digit_bits(bits);
-    for (int shift = 0; shift < bits; shift += dbits) {
-        hipLaunchKernelGGL(k_radix_hist, dim3(tiles), dim3(kBlock), 0, stream, kin, np, shift, dbits,
-                           hist);
-        device_scan(hist, int64_t(tiles) << dbits, small + 3, sums, stream);
-        hipLaunchKernelGGL(k_radix_scatter, dim3(tiles), dim3(kBlock), 0, stream, kin, vin, np, shift,
-                           dbits, hist, kout, vout);
-        BEVPOOL_HIP(hipGetLastError());
-        std::swap(kin, kout);
-        std::swap(vin, vout);
-    }
-    if (vin != sorted_point)
-        BEVPOOL_HIP(hipMemcpyAsync(sorted_point, vin, sizeof(int32_t) * size_t(np),
-                                   hipMemcpyDeviceToDevice, stream));
-    hipLaunchKernelGGL(k_cell_start, dim3(blocks_for(int64_t(np) + 1)), dim3(kBlock), 0, stream, kin,
+    uint32_t *skeys = keys_a;
+    int32_t *sids = odd_passes ? vals_b : sorted_point;
+    rc = radix_sort(cell_of_point, n_cells, skeys, keys_b, sids, odd_passes ? sorted_point : vals_b, np, bits, hist,
+                    sums, stream);
+    if (rc != BEVPOOL_OK) return rc;
+    hipLaunchKernelGGL(k_cell_start, dim3(blocks_for(int64_t(np) / kStartItems + 1)), dim3(kBlock), 0, stream, skeys,
                        np, n_cells, cell_start);
     BEVPOOL_HIP(hipGetLastError());
     return BEVPOOL_OK;
