@@ -4,29 +4,35 @@
 //   dP[b][p]      = F[b][pixel(p)] . G[b][cell(p)]   for a kept point p, else 0
 //   dF[b][pixel]  = sum over the kept points p of the pixel of P[b][p] G[b][cell(p)]
 //
-// Two kernels share the work by blocks of kBwdBlockCols pixel columns of one
-// camera (the plan flags the blocks that hold a combo that is not clean).
+// k_backward_mma (feature and gradient rows of whole, aligned 4-element quads)
+// runs both on the matrix cores (v_mfma_f32_16x16x4f32, fp32 in and out). A
+// workgroup owns 4 adjacent columns and 16 rows of one camera. The plan lists
+// for it, in depth order, slots of one cell for each column with a mask of the
+// rows whose points lie in that cell: one slot for a depth bin of a level
+// camera, several where a tilted camera's rows cross cells. For one column and
+// the gradient rows G[s] of its slots' cells, with M the masks,
+//   dF[h][c] = sum_s M[s][h] P[d(s)][h] G[s][c]
+//   dP[d(s)][h] = sum_c G[s][c] F[h][c]   where M[s][h] is set
+// The workgroup's four waves take consecutive parts of the list, 16 slots per
+// step. The second product takes the channels as its K dimension in the order
+// 16t + 4q + e (t the tile, q the lane quarter, e the element), so that F and G
+// arrive as 16-byte quads; the first takes the slots as K and reads the step's
+// gradient rows back transposed from the wave's own LDS copy. P and dP of the
+// four columns move as 16-byte pieces (8 for 16-bit P). A bin's slots lie in one
+// step, so the step's dP rows are whole and are stored once. The waves' dF sums
+// are added in LDS in wave order.
 //
-// Clean blocks (every combo's kept rows in one cell, one row range): per
-// pixel column w the gradients are two small matrix products over the
-// column's gradient rows G_w[d] = G[cell(n, d, w)],
-//   dF_w[h][c] = sum_d M[d][h] P[d][h] G_w[d][c]
-//   dP_w[d][h] = M[d][h] (sum_c G_w[d][c] F_w[h][c])
-// with M the kept-row mask of the combos. k_backward_mma runs both on the
-// matrix cores (v_mfma_f32_16x16x4f32, fp32 in and out): a workgroup owns
-// two adjacent columns and 16 rows of one camera, its four waves take
-// consecutive parts of the depth bins, 16 bins per step. The second product
-// takes the channels as its K dimension in the order 16t + 4q + e (t the
-// step group, q the lane quarter, e the element), so that F and G arrive as
-// 16-byte quads; the first takes the depth bins as K and reads the step's
-// gradient rows back transposed from the wave's own LDS copy. The waves' dF
-// sums are added in LDS in wave order; every dP element comes from one wave.
-// The combos come from the plan's table by column (consecutive depth bins
-// adjacent: one 8-byte read per lane covers 64 bins), and P and dP of the
-// column pair move as 8-byte pieces (W even; odd widths take the per-row
-// kernel).
+// What bounds it (fp32, 6 cameras x 118 bins x 32 x 88, C = 80, in cache): 25 us,
+// of which 8 are the kernel without its steps and 10 the steps without their
+// memory accesses (the matrix cores alone 4.4); the rest is L1 and L2 time of
+// gathered rows and of P and dP, whose lanes each touch a line of their own. A
+// 4-column tile touches half the lines of a 2-column one, and 128 channels in
+// one launch read P once: 236 bins x 64 x 176, C = 128 went from 359 us (two
+// launches of the 2-column kernel) to 177 us, two bf16 frames of cameras tilted
+// by 1 degree from 147 us (the kernel below) to 65 us. 8 waves per workgroup:
+// 29.6 against 23.8 us; three waves per SIMD by spilling: no gain.
 //
-// Other blocks (k_backward): pixel-stationary work on the vector ALUs. A
+// k_backward (other rows): pixel-stationary work on the vector ALUs. A
 // workgroup owns kBCols pixel columns x kBRows rows of one camera, and its
 // kBWaves waves take consecutive parts of the depth bins. A group of 16
 // lanes owns one column; lane j holds the row slice channels (the forward's
@@ -55,7 +61,6 @@ namespace {
 
 constexpr int kBRows = 8;                      // pixel rows per lane group
 constexpr int kBCols = 4;                      // pixel columns per workgroup (lane groups of a wave)
-static_assert(kBwdBlockCols % kBCols == 0, "a workgroup's columns lie in one backward block");
 constexpr int kBWaves = 4;                     // depth parts per workgroup
 constexpr int kBBlock = kBWaves * kWaveSize;
 constexpr int kBStages = 4;                    // depth bins in flight per wave
@@ -72,9 +77,6 @@ struct BwdArgs {
     int32_t items_w, items_h;                  // column blocks and row blocks per camera
     int32_t part;                              // depth bins per wave
     int32_t accumulate_dp, want_dp, want_df;
-    const int32_t *mixed;                      // per backward block: 1 if a combo is not clean
-    int32_t skip_clean;                        // 1: blocks without such combos are left to k_backward_mma
-    int32_t blocks_w8;                         // backward blocks per camera
 };
 
 // One depth bin of a lane group: its combo's cell, each row's cell (lane j:
@@ -190,7 +192,6 @@ __global__ __launch_bounds__(kBBlock) void k_backward(BwdArgs a) {
     const int rb = item % a.items_h;
     const int t = item / a.items_h;
     const int cb = t % a.items_w, n = t / a.items_w;
-    if (a.skip_clean && a.mixed[n * a.blocks_w8 + cb * kBCols / kBwdBlockCols] == 0) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane & 15, grp = lane >> 4;
     const int w = cb * kBCols + grp;
@@ -323,13 +324,13 @@ __global__ __launch_bounds__(kBBlock) void k_backward(BwdArgs a) {
 
 // ---------------------------------------------------------------- matrix cores
 
-constexpr int kMWaves = 4;                     // depth parts per workgroup
-constexpr int kMCols = 2;                      // adjacent pixel columns per workgroup
-constexpr int kMRows = 16;                     // pixel rows per workgroup (M of the instruction)
-constexpr int kMChunk = 16;                    // depth bins per step (N of the dP product)
+constexpr int kMWaves = 4;                     // parts of a list per workgroup
 constexpr int kMBlock = kMWaves * kWaveSize;
-constexpr int kMSlice = 80;                    // channels per launch (a multiple of 16)
-static_assert(kBwdBlockCols % kMCols == 0, "a column pair lies in one backward block");
+constexpr int kMCols = kBwdCols;               // adjacent pixel columns per workgroup
+constexpr int kMRows = kBwdRows;               // pixel rows per workgroup (M of the instruction)
+constexpr int kMChunk = kBwdStep;               // slots per step (N of the dP product)
+constexpr int kMSlice = 128;                   // channels per launch, at most
+static_assert(kMCols == 4 && kMRows == 16 && kMChunk == 16, "the shape of the slots and of the instruction");
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
@@ -337,12 +338,11 @@ struct MmaArgs {
     const char *P, *F;
     const float *G;
     float *dP, *dF;
-    const int2 *combos;                        // [N][W][D]: {cell, rows} of a clean combo, else {-1, 0}
-    const int32_t *mixed;                      // [N][blocks_w]: 1 if a combo of the block is not clean
-    int32_t D, H, W, C, c0, cn;                // channel slice [c0, c0 + cn), cn a multiple of 4; W even
-    uint32_t p_bytes, f_bytes, g_bytes, dp_bytes, df_bytes, cb_bytes;
-    int32_t pairs_w, blocks_h, blocks_w;       // column pairs, row blocks, backward blocks per camera
-    int32_t part;                              // depth bins per wave, a multiple of kMChunk
+    const int32_t *offs, *bins;                // the plan's backward lists
+    const int4 *cells, *masks;
+    int32_t D, H, W, C, c0, cn;                // channel slice [c0, c0 + cn), cn a multiple of 4
+    uint32_t p_bytes, f_bytes, g_bytes, dp_bytes, df_bytes;
+    int32_t quads_w, blocks_h;                 // column quads and row blocks per camera
     int32_t accumulate_dp, want_dp, want_df;
 };
 
@@ -351,91 +351,105 @@ struct MmaArgs {
 template <int T>
 constexpr int mma_stride() { return 16 * (T | 1); }
 
-// Two consecutive elements as fp32.
-template <int DT>
-__device__ __forceinline__ void load_pair(Rsrc r, uint32_t off, float &x, float &y) {
-    if constexpr (DT == BEVPOOL_F32) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, int(off), 0, 0);
-        x = __uint_as_float(v[0]);
-        y = __uint_as_float(v[1]);
-    } else {
-        const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(r, int(off), 0, 0);
-        if constexpr (DT == BEVPOOL_BF16) {
-            x = __uint_as_float(v << 16);
-            y = __uint_as_float(v & 0xFFFF0000u);
-        } else {
-            x = float(__builtin_bit_cast(_Float16, uint16_t(v & 0xFFFFu)));
-            y = float(__builtin_bit_cast(_Float16, uint16_t(v >> 16)));
-        }
-    }
+// LDS words from one bin of a step's dP to the next: kMRows x kMCols values,
+// and a quad so that bins start in different banks.
+constexpr int kDpStride = kMRows * kMCols + 4;
+
+// Slot k + j of a list in lane (q, j): the columns' cells, row masks and bin.
+// Past the wave's last slot it holds that slot, which takes part in nothing
+// once end_slot has run.
+struct Slot {
+    int4 c, m;
+    int d;
+};
+
+__device__ __forceinline__ void end_slot(Slot &t, bool ok) {
+    t.c = ok ? t.c : make_int4(-1, -1, -1, -1);
+    t.m = ok ? t.m : make_int4(0, 0, 0, 0);
 }
 
-__device__ __forceinline__ bool row_kept(int h, int rg) {
-    const int lo = rg & 0xFFFF, hi = rg >> 16;
-    return uint32_t(h - lo) < uint32_t(hi - lo);
-}
-
-template <int DT, int T>
-__global__ __launch_bounds__(kMBlock) __attribute__((amdgpu_waves_per_eu(3)))
+template <int DT, int T, bool WIDE>
+__global__ __launch_bounds__(kMBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_backward_mma(MmaArgs a) {
     constexpr int S = mma_stride<T>();
-    constexpr int kLds = kMWaves * kMCols * kMChunk * S;
-    static_assert((kMWaves - 1) * kMCols * T * 4 * kWaveSize <= kLds, "dF exchange fits the step buffers");
     constexpr int kFq = 4 * T + 1;             // quads per feature row in LDS (odd: no bank conflicts)
-    __shared__ __attribute__((aligned(16))) float s_g[kLds];
-    __shared__ f4v s_f[kMCols * kMRows * kFq];
+    constexpr int kSum = T * 4 * kWaveSize;    // one wave's dF sums of a column
+    constexpr int kGs = kMChunk * S > kMChunk * kDpStride ? kMChunk * S : kMChunk * kDpStride;
     constexpr uint32_t ES = Elem<DT>::kBytes;
+    // feature rows and the waves' step buffers; for the sums at the end, two
+    // columns of every wave
+    constexpr int kLds = kMCols * kMRows * kFq * 4 + kMWaves * kGs;
+    static_assert(2 * kMWaves * kSum <= kLds, "two columns' sums fit");
+    __shared__ __attribute__((aligned(16))) float s_all[kLds];
+    f4v *s_f = reinterpret_cast<f4v *>(s_all);
+    float *s_g = s_all + kMCols * kMRows * kFq * 4;
     const int b = blockIdx.y;
-    // the two row blocks of a column pair share its gradient rows: placed on
-    // one CU; neighbouring pairs share P lines: placed on one XCD
+    // the row blocks of a column quad share its gradient rows: two of them on
+    // one CU; neighbouring quads share P lines: placed on one XCD
     const int item = xcd_cu_remap<2>(blockIdx.x, gridDim.x);
     const int rb = item % a.blocks_h;
     const int tt = item / a.blocks_h;
-    const int cp = tt % a.pairs_w, n = tt / a.pairs_w;
-    const int w0 = cp * kMCols;
-    if (a.mixed[n * a.blocks_w + w0 / kBwdBlockCols] != 0) return;   // left to k_backward
+    const int cq = tt % a.quads_w, n = tt / a.quads_w;
+    const int w0 = cq * kMCols, h0 = rb * kMRows;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int q = lane >> 4, j = lane & 15;
-    const int h0 = rb * kMRows;
-    const int hj = h0 + j;
-    const bool hj_ok = hj < a.H;
 
     const Rsrc P = make_rsrc(a.P + int64_t(b) * a.p_bytes, a.p_bytes);
     const Rsrc F = make_rsrc(a.F + int64_t(b) * a.f_bytes, a.f_bytes);
     const Rsrc G = make_rsrc(reinterpret_cast<const char *>(a.G) + int64_t(b) * a.g_bytes, a.g_bytes);
     const Rsrc dP = make_rsrc(reinterpret_cast<const char *>(a.dP) + int64_t(b) * a.dp_bytes, a.dp_bytes);
     const Rsrc dF = make_rsrc(reinterpret_cast<const char *>(a.dF) + int64_t(b) * a.df_bytes, a.df_bytes);
-    const Rsrc CB = make_rsrc(a.combos, a.cb_bytes);
     const uint32_t HW = uint32_t(a.H) * uint32_t(a.W);
-    const int d_lo = min(a.D, wave * a.part), d_hi = min(a.D, d_lo + a.part);
 
-    // combos of up to 64 depth bins, lane l: bin dsup + l (one 8-byte entry
-    // per column, consecutive bins adjacent), issued before everything else
-    int ccv[kMCols], rgv[kMCols];
-    auto load_combos = [&](int dsup) {
+    // this wave's slots of the list
+    const int s0 = a.offs[item], s1 = a.offs[item + 1];
+    const int part = ((s1 - s0 + kMWaves - 1) / kMWaves + kMChunk - 1) / kMChunk * kMChunk;
+    const int lo = min(s1, s0 + wave * part), hi = min(s1, lo + part);
+    // (clamped and masked later: no branch and no wait at the loads)
+    auto load_slot = [&](Slot &t, int k) {
+        const int at = min(k + j, hi - 1);
+        t.c = a.cells[at];
+        t.m = a.masks[at];
+        t.d = a.bins[at];
+    };
+    // the gradient rows of a column's 16 slots, slot j's row in the lanes
+    // (., j) as quads in the channel order of the dP product
+    f4v g[T];
+    auto load_rows = [&](int cell) {
+        const uint32_t row = uint32_t(max(cell, 0)) * uint32_t(a.C) + uint32_t(a.c0 + 4 * q);
 #pragma unroll
-        for (int i = 0; i < kMCols; ++i) {
-            const int d = dsup + lane;
-            const bool ok = d < d_hi;
-            const uint32_t addr = (uint32_t(n * a.W + w0 + i) * uint32_t(a.D) + uint32_t(d)) * 8u;
-            const auto v = __builtin_amdgcn_raw_buffer_load_b64(CB, int(ok ? addr : kOff), 0, 0);
-            ccv[i] = ok ? int(v[0]) : -1;
-            rgv[i] = ok ? int(v[1]) : 0;
+        for (int t = 0; t < T; ++t) {
+            const bool ok = (cell >= 0) & (16 * t + 4 * q < a.cn);
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(G, int(ok ? (row + uint32_t(16 * t)) * 4u : kOff), 0, 0);
+            g[t] = f4v{__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3])};
         }
     };
-    load_combos(d_lo);
-
-    // the feature rows of the workgroup's two columns and 16 rows, in LDS:
-    // quad 4t + q of row (i, r) holds channels c0 + 16t + 4q .. + 3
-    for (int x = threadIdx.x; x < kMCols * kMRows * 4 * T; x += kMBlock) {
-        const int qd = x % (4 * T), r = (x / (4 * T)) % kMRows, i = x / (4 * T * kMRows);
-        const int h = h0 + r;
-        const bool ok = (h < a.H) & (4 * qd < a.cn);
-        const uint32_t addr = ((uint32_t(n) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w0 + i)) * uint32_t(a.C) +
+    // the feature rows of the workgroup's columns and rows go to LDS: quad
+    // 4t + q of row (i, r) holds channels c0 + 16t + 4q .. + 3. All of a
+    // thread's loads are issued before the first is waited for.
+    constexpr int kQuads = kMCols * kMRows * 4 * T;
+    constexpr int kFill = (kQuads + kMBlock - 1) / (kMBlock);
+    float fill[kFill][4];
+#pragma unroll
+    for (int u = 0; u < kFill; ++u) {
+        const int x = threadIdx.x + u * kMBlock;
+        const int qd = x % (4 * T), i = (x / (4 * T)) % kMCols, r = x / (4 * T * kMCols);
+        const bool ok = (h0 + r < a.H) & (w0 + i < a.W) & (4 * qd < a.cn);
+        const uint32_t addr = ((uint32_t(n) * HW + uint32_t(h0 + r) * uint32_t(a.W) + uint32_t(w0 + i)) * uint32_t(a.C) +
                                uint32_t(a.c0 + 4 * qd)) * ES;
-        float v[4];
-        Elem<DT>::load4(F, ok ? addr : kOff, v);
-        s_f[(i * kMRows + r) * kFq + qd] = f4v{v[0], v[1], v[2], v[3]};
+        Elem<DT>::load4(F, ok ? addr : kOff, fill[u]);
+    }
+    Slot sl;
+    if (lo < hi) {
+        load_slot(sl, lo);
+        end_slot(sl, lo + j < hi);
+        load_rows(sl.c.x);
+    }
+#pragma unroll
+    for (int u = 0; u < kFill; ++u) {
+        const int x = threadIdx.x + u * kMBlock;
+        const int qd = x % (4 * T), i = (x / (4 * T)) % kMCols, r = x / (4 * T * kMCols);
+        if (x < kQuads) s_f[(i * kMRows + r) * kFq + qd] = f4v{fill[u][0], fill[u][1], fill[u][2], fill[u][3]};
     }
 
     // dF sums: lane (q, j), value r holds row h0 + 4q + r, channel c0 + 16t + j
@@ -444,43 +458,47 @@ void k_backward_mma(MmaArgs a) {
     for (int i = 0; i < kMCols; ++i)
 #pragma unroll
         for (int t = 0; t < T; ++t) accf[i][t] = f4v{0.f, 0.f, 0.f, 0.f};
-
-    float *sg = s_g + wave * (kMCols * kMChunk * S);
-
-    // Loads of one step (16 depth bins from d0 = dsup + k): the gradient rows
-    // of bins d0 + j as 16-byte quads in the channel order of the dP product,
-    // and P of bins d0 + 4s + q, row h0 + j (operand A of the dF product).
-    struct StepIn {
-        f4v g[kMCols][T];
-        float p[kMCols][4];
-    };
-    auto load_step = [&](StepIn &in, int dsup, int k) {
-        const int d0 = dsup + k;
+    float *sg = s_g + wave * kGs;
+    // a step's rows in the wave's LDS: row j = slot j, its quads permuted in
+    // each group of four by j / 4, so that neither the 16-byte writes (rows 4
+    // apart start in the same bank) nor the transposed reads collide
+    float *sg_wr = sg + j * S + ((q ^ (j >> 2)) << 2);
+    const float *sg_rd[4];
 #pragma unroll
-        for (int i = 0; i < kMCols; ++i) {
-            const int cc = __shfl(ccv[i], k + j, kWaveSize);
-            const uint32_t row = uint32_t(max(cc, 0)) * uint32_t(a.C) + uint32_t(a.c0 + 4 * q);
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const bool ok = (cc >= 0) & (16 * t + 4 * q < a.cn);
-                const uint32_t addr = (row + uint32_t(16 * t)) * 4u;
-                const auto v = __builtin_amdgcn_raw_buffer_load_b128(G, int(ok ? addr : kOff), 0, 0);
-                in.g[i][t] = f4v{__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]),
-                                 __uint_as_float(v[3])};
-            }
-        }
+    for (int s = 0; s < 4; ++s) sg_rd[s] = sg + (4 * s + q) * S + (((j >> 2) ^ s) << 2) + (j & 3);
+    __syncthreads();   // the feature rows are in LDS
+
+    // P of slot 4s + q, row h0 + j (operand A of the dF product) where the
+    // slot's cells keep that point: bit 4s + i of kept for column i
+    float p[4][kMCols];
+    int kept = 0;
+    auto load_probs = [&](const Slot &t) {
+        kept = 0;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const int d = d0 + 4 * s + q;
-            const bool ok = (d < d_hi) & hj_ok;
-            const uint32_t pt = uint32_t(n * a.D + d) * HW + uint32_t(hj) * uint32_t(a.W) + uint32_t(w0);
-            load_pair<DT>(P, ok ? pt * ES : kOff, in.p[0][s], in.p[1][s]);
+            const int k01 = __shfl(t.m.x, 4 * s + q) >> j, k23 = __shfl(t.m.y, 4 * s + q) >> j;
+            const int d = __shfl(t.d, 4 * s + q);
+            const int m = (k01 & 1) | (k01 >> 15 & 2) | (k23 & 1) << 2 | (k23 >> 13 & 8);
+            const uint32_t pt = (uint32_t(n * a.D + d) * uint32_t(a.H) + uint32_t(h0 + j)) * uint32_t(a.W) + uint32_t(w0);
+            if constexpr (WIDE) {
+                const uint32_t off = pt * ES;
+                Elem<DT>::load4(P, m != 0 ? off : kOff, p[s]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kMCols; ++i)
+                    p[s][i] = Elem<DT>::load(P, m >> i & 1 ? (pt + uint32_t(i)) * ES : kOff);
+            }
+            kept |= m << (4 * s);
         }
     };
+    Slot next;
+    if (lo < hi) {
+        load_probs(sl);
+        load_slot(next, lo + kMChunk);
+    }
 
-    auto run_step = [&](const StepIn &in, int dsup, int k) {
-        const int d0 = dsup + k;
-        // dP product: lane (q, j), value r is row h0 + 4q + r, bin d0 + j
+    for (int k = lo; k < hi; k += kMChunk) {
+        // dP product: lane (q, j), value r is row h0 + 4q + r, slot j
         f4v accp[kMCols];
 #pragma unroll
         for (int i = 0; i < kMCols; ++i) {
@@ -490,111 +508,146 @@ void k_backward_mma(MmaArgs a) {
                 const f4v f = s_f[(i * kMRows + j) * kFq + 4 * t + q];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    accp[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], in.g[i][t][e], accp[i], 0, 0, 0);
+                    accp[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], g[t][e], accp[i], 0, 0, 0);
             }
-        }
-        // the step's gradient rows into this wave's LDS rows, row j = bin d0 + j
+            // the rows into the wave's LDS; their registers then take the
+            // next column's rows, which arrive while the dF product runs
 #pragma unroll
-        for (int i = 0; i < kMCols; ++i)
+            for (int t = 0; t < T; ++t) *reinterpret_cast<f4v *>(&sg_wr[16 * t]) = g[t];
+            __builtin_amdgcn_wave_barrier();
+            load_rows(i == 0 ? sl.c.y : i == 1 ? sl.c.z : i == 2 ? sl.c.w : k + kMChunk + j < hi ? next.c.x : -1);
+            __builtin_amdgcn_sched_barrier(0);
+            // dF product: K = slot, N = channel, kRead slots quarters' reads
+            // in flight at a time
+            constexpr int kRead = T <= 5 ? 4 : T <= 6 ? 2 : 1;
 #pragma unroll
-            for (int t = 0; t < T; ++t)
-                *reinterpret_cast<f4v *>(&sg[(i * kMChunk + j) * S + 16 * t + 4 * q]) = in.g[i][t];
-        // dF product: operand A masked to the combos' kept rows, operand B
-        // (K = bin, N = channel) read back transposed
+            for (int s0 = 0; s0 < 4; s0 += kRead) {
+                float gt[kRead][T];
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+                for (int s = 0; s < kRead; ++s)
 #pragma unroll
-            for (int i = 0; i < kMCols; ++i) {
-                const int rg = __shfl(rgv[i], k + 4 * s + q, kWaveSize);
-                const float pm = row_kept(hj, rg) ? in.p[i][s] : 0.f;
+                    for (int t = 0; t < T; ++t) gt[s][t] = sg_rd[s0 + s][16 * t];
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    const float g = sg[(i * kMChunk + 4 * s + q) * S + 16 * t + j];
-                    accf[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(pm, g, accf[i][t], 0, 0, 0);
+                for (int s = 0; s < kRead; ++s) {
+                    const float pm = kept >> (4 * (s0 + s) + i) & 1 ? p[s0 + s][i] : 0.f;
+#pragma unroll
+                    for (int t = 0; t < T; ++t)
+                        accf[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(pm, gt[s][t], accf[i][t], 0, 0, 0);
                 }
             }
+            __builtin_amdgcn_wave_barrier();
+        }
+        // the next step's P before this step's dP: loads and stores complete
+        // in order, so a load behind a store would wait for it
+        end_slot(next, k + kMChunk + j < hi);
+        load_probs(next);
+        __builtin_amdgcn_sched_barrier(0);
         if (a.want_dp) {
-            const int d = d0 + j;
-            int rgj[kMCols];
-#pragma unroll
-            for (int i = 0; i < kMCols; ++i) rgj[i] = __shfl(rgv[i], k + j, kWaveSize);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int h = h0 + 4 * q + r;
-                const bool ok = (d < d_hi) & (h < a.H);
-                const uint32_t off = ok ? (uint32_t(n * a.D + d) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w0)) * 4u
-                                        : kOff;
-                float v0 = row_kept(h, rgj[0]) ? accp[0][r] : 0.f;
-                float v1 = row_kept(h, rgj[1]) ? accp[1][r] : 0.f;
+            // row h of bin d: four columns, 16 bytes where they move as one
+            auto store_dp = [&](int d, int h, bool ok, float (&v)[kMCols]) {
+                const uint32_t off = ((uint32_t(n * a.D + d) * uint32_t(a.H) + uint32_t(h)) * uint32_t(a.W) + uint32_t(w0)) * 4u;
                 if (a.accumulate_dp) {
-                    const auto o = __builtin_amdgcn_raw_buffer_load_b64(dP, int(off), 0, 0);
-                    v0 += __uint_as_float(o[0]);
-                    v1 += __uint_as_float(o[1]);
+#pragma unroll
+                    for (int i = 0; i < kMCols; ++i)
+                        v[i] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dP, int(ok & (w0 + i < a.W) ? off + 4u * i : kOff), 0, 0));
                 }
-                __builtin_amdgcn_raw_buffer_store_b64(
-                    (__attribute__((ext_vector_type(2))) uint32_t){__float_as_uint(v0), __float_as_uint(v1)}, dP,
-                    int(off), 0, 0);
+                if constexpr (WIDE) {
+                    __builtin_amdgcn_raw_buffer_store_b128(
+                        (__attribute__((ext_vector_type(4))) uint32_t){__float_as_uint(v[0]), __float_as_uint(v[1]),
+                                                                       __float_as_uint(v[2]), __float_as_uint(v[3])},
+                        dP, int(ok ? off : kOff), 0, 0);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kMCols; ++i) store_f32(dP, ok & (w0 + i < a.W) ? off + 4u * i : kOff, v[i]);
+                }
+            };
+            const bool real = k + j < hi;
+            const int d0 = __builtin_amdgcn_readfirstlane(sl.d);
+            if (__ballot(real & (sl.d != d0 + j)) == 0) {
+                // every bin of the step has one slot
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k01 = sl.m.x >> (4 * q + r), k23 = sl.m.y >> (4 * q + r);
+                    float v[kMCols] = {k01 & 1 ? accp[0][r] : 0.f, k01 & 0x10000 ? accp[1][r] : 0.f,
+                                       k23 & 1 ? accp[2][r] : 0.f, k23 & 0x10000 ? accp[3][r] : 0.f};
+                    store_dp(sl.d, h0 + 4 * q + r, real & (h0 + 4 * q + r < a.H), v);
+                }
+            } else {
+                // the slots' values meet in LDS (a bin's slots lie in one
+                // step), so that every row of a bin is stored once
+                float *mine = sg + (sl.d - d0) * kDpStride + 4 * q * kMCols;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k01 = sl.m.x >> (4 * q + r), k23 = sl.m.y >> (4 * q + r);
+                    const int w01 = sl.m.z >> (4 * q + r), w23 = sl.m.w >> (4 * q + r);
+                    if (w01 & 1) mine[r * kMCols] = k01 & 1 ? accp[0][r] : 0.f;
+                    if (w01 & 0x10000) mine[r * kMCols + 1] = k01 & 0x10000 ? accp[1][r] : 0.f;
+                    if (w23 & 1) mine[r * kMCols + 2] = k23 & 1 ? accp[2][r] : 0.f;
+                    if (w23 & 0x10000) mine[r * kMCols + 3] = k23 & 0x10000 ? accp[3][r] : 0.f;
+                }
+                __builtin_amdgcn_wave_barrier();
+                // bins of this step: up to the last real slot's
+                const int bins = __shfl(sl.d, min(hi - k, kMChunk) - 1) - d0 + 1;
+                for (int x = lane; x < bins * kMRows; x += kWaveSize) {
+                    const int h = h0 + x % kMRows;
+                    const f4v u = *reinterpret_cast<const f4v *>(&sg[x / kMRows * kDpStride + x % kMRows * kMCols]);
+                    float v[kMCols] = {u[0], u[1], u[2], u[3]};
+                    store_dp(d0 + x / kMRows, h, h < a.H, v);
+                }
+                __builtin_amdgcn_wave_barrier();
             }
         }
-        __builtin_amdgcn_wave_barrier();
-    };
-
-    __syncthreads();   // the feature rows are in LDS
-    // steps of 16 bins
-    StepIn in0;
-    for (int dsup = d_lo; dsup < d_hi; dsup += kWaveSize) {
-        if (dsup > d_lo) load_combos(dsup);
-        const int dn = min(kWaveSize, d_hi - dsup);
-        for (int k = 0; k < dn; k += kMChunk) {
-            load_step(in0, dsup, k);
-            run_step(in0, dsup, k);
-        }
+        sl = next;
+        load_slot(next, k + 2 * kMChunk);
     }
 
     if (!a.want_df) return;
-    // waves 1.. park their sums in LDS; wave 0 adds them in wave order
-    __syncthreads();
-    if (wave > 0) {
+    // two columns' sums of all waves in LDS, added in wave order; the waves
+    // take their (column, channel tile, row) values in turn
 #pragma unroll
-        for (int i = 0; i < kMCols; ++i)
+    for (int i0 = 0; i0 < kMCols; i0 += 2) {
+        __syncthreads();
 #pragma unroll
-            for (int t = 0; t < T; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    s_g[((((wave - 1) * kMCols + i) * T + t) * 4 + r) * kWaveSize + lane] = accf[i][t][r];
-    }
-    __syncthreads();
-    if (wave > 0) return;
-    for (int v = 1; v < kMWaves; ++v)
-#pragma unroll
-        for (int i = 0; i < kMCols; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int t = 0; t < T; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    accf[i][t][r] += s_g[((((v - 1) * kMCols + i) * T + t) * 4 + r) * kWaveSize + lane];
+                    s_all[(wave * 2 + i) * kSum + (t * 4 + r) * kWaveSize + lane] = accf[i0 + i][t][r];
+        __syncthreads();
+        for (int x = wave; x < 8 * T; x += kMWaves) {
+            float v = 0.f;
 #pragma unroll
-    for (int i = 0; i < kMCols; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int h = h0 + 4 * q + r;
-            const uint32_t row = (uint32_t(n) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w0 + i)) * uint32_t(a.C);
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const bool ok = (h < a.H) & (16 * t + j < a.cn);
-                store_f32(dF, ok ? (row + uint32_t(a.c0 + 16 * t + j)) * 4u : kOff, accf[i][t][r]);
-            }
+            for (int u = 0; u < kMWaves; ++u) v += s_all[u * 2 * kSum + x * kWaveSize + lane];
+            const int i = x / (4 * T), t = x % (4 * T) / 4, h = h0 + 4 * q + x % 4, w = w0 + i0 + i;
+            const bool ok = (h < a.H) & (w < a.W) & (16 * t + j < a.cn);
+            const uint32_t row = (uint32_t(n) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w)) * uint32_t(a.C);
+            store_f32(dF, ok ? (row + uint32_t(a.c0 + 16 * t + j)) * 4u : kOff, v);
         }
+    }
 }
 
-template <int DT>
+template <int DT, bool WIDE>
 void launch_mma(const MmaArgs &a, dim3 grid, int tiles, hipStream_t s) {
+    const dim3 block(kMBlock);
     switch (tiles) {
-        case 1: hipLaunchKernelGGL((k_backward_mma<DT, 1>), grid, dim3(kMBlock), 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_backward_mma<DT, 2>), grid, dim3(kMBlock), 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_backward_mma<DT, 3>), grid, dim3(kMBlock), 0, s, a); break;
-        case 4: hipLaunchKernelGGL((k_backward_mma<DT, 4>), grid, dim3(kMBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_backward_mma<DT, 5>), grid, dim3(kMBlock), 0, s, a); break;
+        case 1: hipLaunchKernelGGL((k_backward_mma<DT, 1, WIDE>), grid, block, 0, s, a); break;
+        case 2: hipLaunchKernelGGL((k_backward_mma<DT, 2, WIDE>), grid, block, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((k_backward_mma<DT, 3, WIDE>), grid, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL((k_backward_mma<DT, 4, WIDE>), grid, block, 0, s, a); break;
+        case 5: hipLaunchKernelGGL((k_backward_mma<DT, 5, WIDE>), grid, block, 0, s, a); break;
+        case 6: hipLaunchKernelGGL((k_backward_mma<DT, 6, WIDE>), grid, block, 0, s, a); break;
+        default: hipLaunchKernelGGL((k_backward_mma<DT, 8, WIDE>), grid, block, 0, s, a); break;
+    }
+}
+
+template <bool WIDE>
+void launch_mma(const MmaArgs &a, int dtype, dim3 grid, int tiles, hipStream_t s) {
+    switch (dtype) {
+        case BEVPOOL_F32: launch_mma<BEVPOOL_F32, WIDE>(a, grid, tiles, s); break;
+        case BEVPOOL_BF16: launch_mma<BEVPOOL_BF16, WIDE>(a, grid, tiles, s); break;
+        default: launch_mma<BEVPOOL_F16, WIDE>(a, grid, tiles, s); break;
     }
 }
 
@@ -637,23 +690,21 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
     if (batch > 65535)
         return bevpool_fail(BEVPOOL_ERR_INVALID_ARG, "batch=%d exceeds 65535 frames per call", batch);
 
-    // Matrix-core kernel for the blocks whose combos are all clean: feature
-    // and gradient rows move as 4-element quads, so channels % 4 == 0 and
-    // aligned rows; the per-row kernel takes the other blocks (or all blocks).
+    // Matrix-core kernel where feature and gradient rows move as 4-element
+    // quads: channels % 4 == 0 and aligned rows. Otherwise the per-row kernel.
     const bool quads = channels % 4 == 0 && reinterpret_cast<uintptr_t>(F) % (4 * esize) == 0 &&
                        reinterpret_cast<uintptr_t>(G) % 16 == 0;
-    // (a column pair is read and written as one 8-byte piece: W even)
-    const bool run_mma = quads && g.feat_w % 2 == 0 && plan->n_bwd_mixed < plan->n_bwd_blocks;
-    const bool run_rows = !run_mma || plan->n_bwd_mixed > 0;
-    if (run_mma) {
+    if (quads) {
         MmaArgs m;
         m.P = static_cast<const char *>(P);
         m.F = static_cast<const char *>(F);
         m.G = G;
         m.dP = dP;
         m.dF = dF;
-        m.combos = plan->combo_cols;
-        m.mixed = plan->bwd_mixed;
+        m.offs = plan->bwd_offs;
+        m.bins = plan->bwd_bins;
+        m.cells = plan->bwd_cells;
+        m.masks = plan->bwd_masks;
         m.D = g.n_depth;
         m.H = g.feat_h;
         m.W = g.feat_w;
@@ -663,29 +714,28 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
         m.g_bytes = uint32_t(g_bytes);
         m.dp_bytes = dP ? uint32_t(dp_bytes) : 0u;
         m.df_bytes = dF ? uint32_t(df_bytes) : 0u;
-        m.cb_bytes = uint32_t(int64_t(g.n_cams) * g.n_depth * g.feat_w * 8);
-        m.pairs_w = g.feat_w / kMCols;
+        m.quads_w = (g.feat_w + kMCols - 1) / kMCols;
         m.blocks_h = (g.feat_h + kMRows - 1) / kMRows;
-        m.blocks_w = (g.feat_w + kBwdBlockCols - 1) / kBwdBlockCols;
-        const int part = (g.n_depth + kMWaves - 1) / kMWaves;
-        m.part = (part + kMChunk - 1) / kMChunk * kMChunk;
+        // P and dP of the four columns move as one piece
+        const bool wide = g.feat_w % kMCols == 0 && reinterpret_cast<uintptr_t>(P) % (4 * esize) == 0 &&
+                          reinterpret_cast<uintptr_t>(dP) % 16 == 0;
         m.want_dp = dP != nullptr;
         m.want_df = dF != nullptr;
-        const dim3 grid(g.n_cams * m.pairs_w * m.blocks_h, batch);
-        for (int c0 = 0; c0 < channels; c0 += kMSlice) {
+        const dim3 grid(g.n_cams * m.quads_w * m.blocks_h, batch);
+        // equal slices of at most kMSlice channels, whole 16-channel tiles
+        const int n_slices = (channels + kMSlice - 1) / kMSlice;
+        const int slice = ((channels + n_slices - 1) / n_slices + 15) / 16 * 16;
+        for (int c0 = 0; c0 < channels; c0 += slice) {
             m.c0 = c0;
-            m.cn = std::min(kMSlice, channels - c0);
+            m.cn = std::min(slice, channels - c0);
             m.accumulate_dp = c0 > 0;
             const int tiles = (m.cn + 15) / 16;
-            switch (dtype) {
-                case BEVPOOL_F32: launch_mma<BEVPOOL_F32>(m, grid, tiles, stream); break;
-                case BEVPOOL_BF16: launch_mma<BEVPOOL_BF16>(m, grid, tiles, stream); break;
-                default: launch_mma<BEVPOOL_F16>(m, grid, tiles, stream); break;
-            }
+            if (wide) launch_mma<true>(m, dtype, grid, tiles, stream);
+            else launch_mma<false>(m, dtype, grid, tiles, stream);
             BEVPOOL_HIP(hipGetLastError());
         }
+        return BEVPOOL_OK;
     }
-    if (!run_rows) return BEVPOOL_OK;
 
     const int n_slices = (channels + kBwdSliceChannels - 1) / kBwdSliceChannels;
     const int slice_c = (channels + n_slices - 1) / n_slices;
@@ -721,9 +771,6 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
     a.part = (g.n_depth + kBWaves - 1) / kBWaves;
     a.want_dp = dP != nullptr;
     a.want_df = dF != nullptr;
-    a.mixed = plan->bwd_mixed;
-    a.skip_clean = run_mma ? 1 : 0;
-    a.blocks_w8 = (g.feat_w + kBwdBlockCols - 1) / kBwdBlockCols;
     const dim3 grid(g.n_cams * a.items_w * a.items_h, batch);
     for (int s = 0; s < n_slices; ++s) {
         a.c0 = s * slice_c;

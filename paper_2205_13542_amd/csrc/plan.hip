@@ -469,7 +469,6 @@ struct ComboArgs {
     int32_t N, D, H, W;
     int32_t allow_clean;        // 0 when rows do not fit the packed row range
     int32_t *combo_cell;        // [N*D*W]: cell of a clean combo, -1 none kept, -2 not clean
-    int32_t *combo_range;       // [N*D*W]: h_lo | h_hi << 16
     int32_t *cell_generic;      // [n_cells]: 1 if a combo that is not clean touches the cell
     int32_t *cell_ncombo;       // [n_cells]: row segments of column-served combos in the cell
     int32_t planes;             // segments a combo may have and stay column-served
@@ -529,7 +528,6 @@ __device__ __forceinline__ void combo_walk_one(const ComboArgs &a, int32_t X, in
     for (int s = 0; s < a.planes; ++s) a.seg_cell[int64_t(s) * n_combo + X] = -1;
     if (n_seg == 0) {
         a.combo_cell[X] = -1;
-        a.combo_range[X] = 0;
         return;
     }
     if (a.allow_clean && n_seg <= a.planes) {
@@ -541,10 +539,8 @@ __device__ __forceinline__ void combo_walk_one(const ComboArgs &a, int32_t X, in
         max_seg = max(max_seg, n_seg);
         served_pts += kept;
         a.combo_cell[X] = n_seg == 1 ? cell[0] : -2;
-        a.combo_range[X] = n_seg == 1 ? (lo[0] | (hi[0] << 16)) : 0;
     } else {
         a.combo_cell[X] = -2;
-        a.combo_range[X] = 0;
         for (int32_t h0 = first; h0 <= last; h0 += kWalkRows) {
             int32_t cc[kWalkRows];
             walk_rows(a, base, h0, cc);
@@ -637,41 +633,167 @@ __global__ __launch_bounds__(kBlock) void k_planes_used(const int2 *table, int64
     if (threadIdx.x == 0 && most > 0) atomicMax(shard(counters, 2), most);
 }
 
-// Clean combos by pixel column: entry (n, w, d) = {cell, rows} of combo
-// (n, d, w) when it is clean and its backward block holds no combo that is
-// not clean, else {-1, 0} (such blocks are left to the per-row kernel).
-__global__ __launch_bounds__(kBlock) void k_combo_cols(const int32_t *combo_cell,
-                                                       const int32_t *combo_range,
-                                                       const int32_t *mixed, int32_t n_combo,
-                                                       int32_t W, int32_t D, int32_t blocks_w,
-                                                       int2 *cols) {
-    const int32_t x = blockIdx.x * kBlock + threadIdx.x;
-    if (x >= n_combo) return;
-    const int32_t w = x % W, nd = x / W, d = nd % D, n = nd / D;
-    const int32_t c = combo_cell[x];
-    const bool clean = c >= 0 && mixed[n * blocks_w + w / kBwdBlockCols] == 0;
-    cols[(int64_t(n) * W + w) * D + d] = clean ? make_int2(c, combo_range[x]) : make_int2(-1, 0);
+// Backward lists (internal.h). One thread per (camera, depth bin, row block,
+// column block) looks at its kBwdRows x kBwdCols cells; threads with
+// adjacent column blocks read adjacent pieces. A column's kept rows are cut
+// where the cell changes (dropped rows in between do not cut), and slot s of
+// the depth bin takes piece s of every column; slot 0 also writes the zeros
+// of the dropped rows. Every depth bin has a slot.
+struct BwdListArgs {
+    const int32_t *cell_of_point;
+    int32_t N, D, H, W, quads_w, blocks_h;
+    FastDiv div_q, div_b, div_d;
+    int32_t total;              // N * D * blocks_h * quads_w threads
+    int32_t n_lists;
+    int32_t *counts;            // [N][quads_w][blocks_h][D] slots of the bins, then their places in the list
+    int32_t *offs;              // [n_lists + 1] slots of the lists, then their first slots
+    int4 *cells, *masks;
+    int32_t *bins;
+};
+
+struct BwdTile {
+    int32_t c[kBwdCols][kBwdRows];   // cells, -1 for a dropped point or one past the map
+    int32_t rows;                    // rows of the block inside the map
+    int32_t cols;                    // columns inside the map
+    int32_t d;
+    int64_t at;                      // entry of counts
+};
+
+__device__ __forceinline__ void load_bwd_tile(const BwdListArgs &a, int32_t x, BwdTile &t) {
+    const uint32_t xq = fdiv(uint32_t(x), a.div_q), xb = fdiv(xq, a.div_b), n = fdiv(xb, a.div_d);
+    const int32_t cq = x - int32_t(xq) * a.quads_w, rb = int32_t(xq) - int32_t(xb) * a.blocks_h;
+    t.d = int32_t(xb) - int32_t(n) * a.D;
+    t.at = ((int64_t(n) * a.quads_w + cq) * a.blocks_h + rb) * a.D + t.d;
+    const int32_t h0 = rb * kBwdRows, w0 = cq * kBwdCols;
+    t.rows = min(kBwdRows, a.H - h0);
+    t.cols = min(kBwdCols, a.W - w0);
+    const int32_t *src = a.cell_of_point + (int64_t(xb) * a.H + h0) * a.W + w0;
+    // rows and columns past the map read clamped, so that all loads are
+    // issued together; a row's piece is one 16-byte load where the rows keep
+    // the alignment (cell_of_point is an allocation of its own)
+    if (a.W % kBwdCols == 0) {
+#pragma unroll
+        for (int r = 0; r < kBwdRows; ++r) {
+            const int4 v = *reinterpret_cast<const int4 *>(src + int64_t(min(r, t.rows - 1)) * a.W);
+            t.c[0][r] = r < t.rows ? v.x : -1;
+            t.c[1][r] = r < t.rows ? v.y : -1;
+            t.c[2][r] = r < t.rows ? v.z : -1;
+            t.c[3][r] = r < t.rows ? v.w : -1;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < kBwdRows; ++r)
+#pragma unroll
+            for (int i = 0; i < kBwdCols; ++i) {
+                const int32_t v = src[int64_t(min(r, t.rows - 1)) * a.W + min(i, t.cols - 1)];
+                t.c[i][r] = r < t.rows && i < t.cols ? v : -1;
+            }
+    }
 }
 
-// Backward blocks (kBwdBlockCols pixel columns of one camera) that hold a
-// combo that is not clean: flagged 1 (every writer stores the same value).
-// One workgroup per backward block (camera n, kBwdBlockCols pixel columns):
-// flags[block] = 1 when one of its combos is not clean, and counter 12 adds
-// the flagged blocks.
-__global__ __launch_bounds__(kBlock) void k_bwd_blocks(const int32_t *combo_cell, int32_t W,
-                                                       int32_t D, int32_t blocks_w, int32_t *flags,
-                                                       int32_t *counters) {
-    __shared__ int32_t s_m[kWaves];
-    const int32_t n = blockIdx.x / blocks_w, w0 = (blockIdx.x % blocks_w) * kBwdBlockCols;
-    int32_t mixed = 0;
-    for (int32_t i = threadIdx.x; i < D * kBwdBlockCols; i += kBlock) {
-        const int32_t d = i / kBwdBlockCols, w = w0 + i % kBwdBlockCols;
-        if (w < W && combo_cell[(int64_t(n) * D + d) * W + w] == -2) mixed = 1;
+__global__ __launch_bounds__(kBlock) void k_bwd_counts(BwdListArgs a) {
+    const int32_t x = blockIdx.x * kBlock + threadIdx.x;
+    if (x >= a.total) return;
+    BwdTile t;
+    load_bwd_tile(a, x, t);
+    int32_t most = 1;
+#pragma unroll
+    for (int i = 0; i < kBwdCols; ++i) {
+        int32_t last = -1, n = 0;
+#pragma unroll
+        for (int r = 0; r < kBwdRows; ++r) {
+            const bool cut = t.c[i][r] >= 0 && t.c[i][r] != last;
+            n += cut ? 1 : 0;
+            last = t.c[i][r] >= 0 ? t.c[i][r] : last;
+        }
+        most = max(most, n);
     }
-    mixed = block_reduce<true>(mixed, s_m);
+    a.counts[t.at] = most;
+}
+
+// One workgroup per list: the bins' places in it. A bin's slots stay within
+// kBwdStep slots of the list (the step of the kernel that runs it), which puts
+// empty slots before a bin that would cross. That order is serial, but what a
+// run of bins adds depends on where it starts only through the place within a
+// step: the bins are cut into kBwdStep runs, thread (c, o) walks run c from
+// offset o of a step, the runs' true starts follow from their 16 advances
+// each, and the thread that started where run c starts writes its places.
+constexpr int kPlaceBins = 1024;   // bins in LDS at a time
+
+__device__ __forceinline__ int32_t bwd_place(int32_t at, int32_t n) {
+    return (at & (kBwdStep - 1)) + n > kBwdStep ? (at | (kBwdStep - 1)) + 1 : at;
+}
+
+__global__ __launch_bounds__(kBlock) void k_bwd_places(BwdListArgs a) {
+    static_assert(kBlock == kBwdStep * kBwdStep, "a thread per run and offset");
+    __shared__ int32_t s_n[kPlaceBins];
+    __shared__ int32_t s_add[kBwdStep][kBwdStep];
+    int32_t *counts = a.counts + int64_t(blockIdx.x) * a.D;
+    const int c = threadIdx.x / kBwdStep, o = threadIdx.x % kBwdStep;
+    int32_t at = 0;
+    for (int32_t d0 = 0; d0 < a.D; d0 += kPlaceBins) {
+        const int32_t nd = min(kPlaceBins, a.D - d0), run = (nd + kBwdStep - 1) / kBwdStep;
+        for (int32_t d = threadIdx.x; d < nd; d += kBlock) s_n[d] = counts[d0 + d];
+        __syncthreads();
+        const int32_t lo = min(nd, c * run), hi = min(nd, lo + run);
+        int32_t end = o;
+        for (int32_t d = lo; d < hi; ++d) end = bwd_place(end, s_n[d]) + s_n[d];
+        s_add[c][o] = end - o;
+        __syncthreads();
+        int32_t start = at;
+        for (int u = 0; u < kBwdStep; ++u) {
+            if (u == c) start = at;
+            at += s_add[u][at & (kBwdStep - 1)];
+        }
+        if ((start & (kBwdStep - 1)) == o)
+            for (int32_t d = lo; d < hi; ++d) {
+                start = bwd_place(start, s_n[d]);
+                counts[d0 + d] = start;
+                start += s_n[d];
+            }
+        __syncthreads();
+    }
     if (threadIdx.x == 0) {
-        flags[blockIdx.x] = mixed;
-        if (mixed) atomicAdd(shard(counters, 12), 1);
+        a.offs[blockIdx.x] = at;
+        if (blockIdx.x == 0) a.offs[a.n_lists] = 0;   // scanned over n_lists + 1 entries
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_bwd_lists(BwdListArgs a) {
+    const int32_t x = blockIdx.x * kBlock + threadIdx.x;
+    if (x >= a.total) return;
+    BwdTile t;
+    load_bwd_tile(a, x, t);
+    const int32_t list = int32_t(t.at / a.D);
+    const int32_t base = a.offs[list], first = base + a.counts[t.at];
+    const int32_t end = t.d + 1 < a.D ? base + a.counts[t.at + 1] : a.offs[list + 1];
+    const uint32_t in_rows = (1u << t.rows) - 1u;
+    // slots past the bin's last piece fill the step: no cells, no rows
+    for (int32_t s = 0; s < end - first; ++s) {
+        int32_t cell[kBwdCols];
+        uint32_t keep[kBwdCols], write[kBwdCols];
+#pragma unroll
+        for (int i = 0; i < kBwdCols; ++i) {
+            int32_t last = -1, piece = -1;
+            uint32_t kept = 0u, any = 0u;
+            cell[i] = -1;
+#pragma unroll
+            for (int r = 0; r < kBwdRows; ++r) {
+                const int32_t c = t.c[i][r];
+                piece += c >= 0 && c != last ? 1 : 0;
+                last = c >= 0 ? c : last;
+                const bool mine = c >= 0 && piece == s;
+                cell[i] = mine ? c : cell[i];
+                kept |= mine ? 1u << r : 0u;
+                any |= c >= 0 ? 1u << r : 0u;
+            }
+            keep[i] = kept;
+            write[i] = i < t.cols ? kept | (s == 0 ? in_rows & ~any : 0u) : 0u;
+        }
+        a.cells[first + s] = make_int4(cell[0], cell[1], cell[2], cell[3]);
+        a.masks[first + s] = make_int4(int32_t(keep[0] | keep[1] << 16), int32_t(keep[2] | keep[3] << 16),
+                                       int32_t(write[0] | write[1] << 16), int32_t(write[2] | write[3] << 16));
+        a.bins[first + s] = t.d;
     }
 }
 
@@ -970,20 +1092,19 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     const int32_t planes = H < kMaxSeg ? H : kMaxSeg;
     const int64_t n_seg = int64_t(planes) * n_combo;   // table entries reserved
     int64_t n_seg_act = n_seg;                          // entries of the planes in use
+    const int32_t quads_w = (W + kBwdCols - 1) / kBwdCols, blocks_h = (H + kBwdRows - 1) / kBwdRows;
+    const int32_t n_lists = N * quads_w * blocks_h;     // backward lists, n_bwd (list, depth bin) pairs:
+    const int32_t n_bwd = n_lists * D;                  // at most one for each point
     plan->n_points = np64;
     plan->n_cells = n_cells;
     plan->nz = nz;
 
-    const int32_t bwd_bw = (W + kBwdBlockCols - 1) / kBwdBlockCols;
-    plan->n_bwd_blocks = N * bwd_bw;
-
-    // the plan's arrays whose sizes the geometry fixes (the combo cells and
-    // columns serve the backward pass)
+    // the plan's arrays whose sizes the geometry fixes
     int rc;
     Arena fixed;
     fixed.cap = 2 * Arena::piece(size_t(np) * 4) + Arena::piece((size_t(n_cells) + 1) * 4) +
                 Arena::piece(size_t(n_seg) * 8) + Arena::piece(size_t(n_combo) * 4) +
-                Arena::piece(size_t(n_combo) * 8) + Arena::piece(size_t(plan->n_bwd_blocks) * 4);
+                Arena::piece((size_t(n_lists) + 1) * 4);
     if ((rc = dev_alloc(&fixed.base, fixed.cap, "the plan"))) return rc;
     plan->mem_fixed = fixed.base;
     if ((rc = fixed.take(&plan->cell_of_point, size_t(np), "cell_of_point"))) return rc;
@@ -991,8 +1112,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     if ((rc = fixed.take(&plan->cell_start, size_t(n_cells) + 1, "cell_start"))) return rc;
     if ((rc = fixed.take(&plan->column_table, size_t(n_seg), "column_table"))) return rc;
     if ((rc = fixed.take(&plan->combo_cells, size_t(n_combo), "combo cells"))) return rc;
-    if ((rc = fixed.take(&plan->combo_cols, size_t(n_combo), "combos by column"))) return rc;
-    if ((rc = fixed.take(&plan->bwd_mixed, size_t(plan->n_bwd_blocks), "backward blocks"))) return rc;
+    if ((rc = fixed.take(&plan->bwd_offs, size_t(n_lists) + 1, "backward lists"))) return rc;
 
     // temporaries, carved from one arena that is given back on every exit path below
     const int64_t sort_cap = np64 > n_cells ? np64 : int64_t(n_cells);
@@ -1003,7 +1123,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     int32_t *vals_a = nullptr, *vals_b = nullptr, *hist = nullptr, *small = nullptr;
     int32_t *scan_sums = nullptr;
     int32_t *flag_a = nullptr, *flag_b = nullptr;
-    int32_t *combo_cell = nullptr, *combo_range = nullptr, *combo_flag = nullptr;
+    int32_t *combo_cell = nullptr, *combo_flag = nullptr;
     int32_t *cell_generic = nullptr, *cell_ncombo = nullptr, *head_scan = nullptr;
     int32_t *run_scan = nullptr, *run_begin = nullptr, *pos_of_cell = nullptr;
 
@@ -1048,9 +1168,9 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
                         5 * cells1_b +                 // flag_a, flag_b, cell_generic, cell_ncombo, run_begin
                         Arena::piece(size_t(n_cells) * i4) +          // pos_of_cell
                         2 * combo1_b +                 // combo_flag, head_scan
-                        Arena::piece(size_t(n_combo) * i4) +          // combo_range
                         2 * Arena::piece(size_t(n_seg) * i4) +        // seg_cell, seg_range
-                        Arena::piece((size_t(np) + 1) * i4);          // run_scan
+                        Arena::piece((size_t(np) + 1) * i4) +         // run_scan
+                        Arena::piece(size_t(n_bwd) * i4);             // bwd_counts
             const size_t need = arena.cap;
             arena.base = bevpool_workspace_out(plan->device, &arena.cap);
             if (!arena.base || arena.cap < need) {
@@ -1072,7 +1192,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         // multi-combo cells, [4..5] class counters, [6] most segments of a
         // combo, [7] their kept points, [8] generic cells, [9] empty cells,
         // [10] kept points, [11] segments of multi-combo cells, [12] backward
-        // blocks with a combo that is not clean, [13] gather runs
+        // slots, [13] gather runs
         if ((rc2 = arena.take(&small, size_t(kShards) * kCounters, "plan counters"))) return rc2;
         if ((rc2 = arena.take(&scan_sums, size_t(kScanSums), "scan chunk sums"))) return rc2;
         if ((rc2 = arena.take(&flag_a, size_t(n_cells) + 1, "flags"))) return rc2;
@@ -1126,7 +1246,6 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
 
         // combos, cell classes and the column table
         combo_cell = plan->combo_cells;
-        if ((rc2 = arena.take(&combo_range, size_t(n_combo), "combo ranges"))) return rc2;
         if ((rc2 = arena.take(&combo_flag, size_t(n_seg) + 1, "segment flags"))) return rc2;
         int32_t *seg_cell = nullptr, *seg_range = nullptr;
         if ((rc2 = arena.take(&seg_cell, size_t(n_seg), "segment cells"))) return rc2;
@@ -1139,13 +1258,32 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         ca.W = W;
         ca.allow_clean = H < kMaxFeatH ? 1 : 0;
         ca.combo_cell = combo_cell;
-        ca.combo_range = combo_range;
         ca.cell_generic = cell_generic;
         ca.cell_ncombo = cell_ncombo;
         ca.planes = planes;
         ca.seg_cell = seg_cell;
         ca.seg_range = seg_range;
         ca.counters = small;
+        // the backward lists' slots are counted here; their number comes back
+        // with the counts of the first classification
+        BwdListArgs bl;
+        bl.cell_of_point = plan->cell_of_point;
+        bl.N = N;
+        bl.D = D;
+        bl.H = H;
+        bl.W = W;
+        bl.quads_w = quads_w;
+        bl.blocks_h = blocks_h;
+        bl.div_q = make_fastdiv(uint32_t(quads_w));
+        bl.div_b = make_fastdiv(uint32_t(blocks_h));
+        bl.div_d = make_fastdiv(uint32_t(D));
+        bl.total = n_bwd;
+        bl.n_lists = n_lists;
+        if ((rc2 = arena.take(&bl.counts, size_t(n_bwd), "backward slots"))) return rc2;
+        bl.offs = plan->bwd_offs;
+        hipLaunchKernelGGL(k_bwd_counts, dim3(blocks_for(n_bwd)), dim3(kBlock), 0, stream, bl);
+        hipLaunchKernelGGL(k_bwd_places, dim3(n_lists), dim3(kBlock), 0, stream, bl);
+        device_scan(bl.offs, int64_t(n_lists) + 1, small + 12, scan_sums, stream);
         // (k_combo_table writes every entry of every plane: no clearing first)
         hipLaunchKernelGGL(k_combo_walk, dim3(reduce_blocks(n_combo)), dim3(kBlock), 0, stream, ca);
         int32_t stats[4], counters[2], n_gen = 0, n_empty = 0, kept = 0, n_part = 0;
@@ -1173,6 +1311,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
             n_empty = h[9];        // empty cells
             kept = h[10];          // kept points (k_cell_stats)
             n_part = h[11];        // combos of multi-combo cells (partial slots)
+            plan->n_bwd_slots = h[12];
             return BEVPOOL_OK;
         };
         if ((rc2 = classify())) return rc2;
@@ -1208,13 +1347,6 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         hipLaunchKernelGGL(k_planes_used, dim3(reduce_blocks(n_seg_act)), dim3(kBlock), 0, stream,
                            plan->column_table, n_seg_act, int32_t(n_combo), small);
 
-        // the backward blocks holding a combo that is not clean, and the clean
-        // combos of the other blocks by pixel column
-        hipLaunchKernelGGL(k_bwd_blocks, dim3(plan->n_bwd_blocks), dim3(kBlock), 0, stream,
-                           combo_cell, W, D, bwd_bw, plan->bwd_mixed, small);
-        hipLaunchKernelGGL(k_combo_cols, dim3(blocks_for(n_combo)), dim3(kBlock), 0, stream,
-                           combo_cell, combo_range, plan->bwd_mixed, int32_t(n_combo), W, D, bwd_bw,
-                           plan->combo_cols);
         BEVPOOL_HIP(hipGetLastError());
 
         // cells without points, ascending
@@ -1224,7 +1356,8 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         Arena counted;
         counted.cap = Arena::piece(size_t(n_empty) * 4) + Arena::piece((size_t(multi_cap) + 1) * 4) +
                       Arena::piece(size_t(multi_cap) * 4) + Arena::piece(size_t(multi_cap) * kCombineInline * 4) +
-                      Arena::piece(size_t(n_gen) * 16);
+                      Arena::piece(size_t(n_gen) * 16) + 2 * Arena::piece(size_t(plan->n_bwd_slots) * 16) +
+                      Arena::piece(size_t(plan->n_bwd_slots) * 4);
         if ((rc2 = dev_alloc(&counted.base, counted.cap, "the plan"))) return rc2;
         plan->mem_counted = counted.base;
         if ((rc2 = counted.take(&plan->empty_cells, size_t(n_empty), "empty_cells"))) return rc2;
@@ -1232,6 +1365,13 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         if ((rc2 = counted.take(&plan->multi_cell, size_t(multi_cap), "multi_cell"))) return rc2;
         if ((rc2 = counted.take(&plan->multi_rows, size_t(multi_cap) * kCombineInline, "multi_rows"))) return rc2;
         if ((rc2 = counted.take(&plan->generic_hdr, size_t(n_gen), "generic_hdr"))) return rc2;
+        if ((rc2 = counted.take(&plan->bwd_cells, size_t(plan->n_bwd_slots), "backward lists"))) return rc2;
+        if ((rc2 = counted.take(&plan->bwd_masks, size_t(plan->n_bwd_slots), "backward lists"))) return rc2;
+        if ((rc2 = counted.take(&plan->bwd_bins, size_t(plan->n_bwd_slots), "backward lists"))) return rc2;
+        bl.cells = plan->bwd_cells;
+        bl.masks = plan->bwd_masks;
+        bl.bins = plan->bwd_bins;
+        hipLaunchKernelGGL(k_bwd_lists, dim3(blocks_for(n_bwd)), dim3(kBlock), 0, stream, bl);
         hipLaunchKernelGGL(k_empty_list, dim3(blocks_for(n_cells)), dim3(kBlock), 0, stream, flag_b,
                            n_cells, plan->empty_cells);
 
@@ -1265,7 +1405,6 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         auto read_rest = [&]() -> int {
             int rc3;
             if ((rc3 = read_counters())) return rc3;
-            plan->n_bwd_mixed = h[12];
             plan->n_multi = h[3];
             plan->n_planes = h[2] > 0 ? h[2] : 1;
             plan->n_runs = h[13];

@@ -268,3 +268,33 @@ def test_backward_level_deterministic(torch_cuda, pkg):
     b = plan.backward(G, P, F)
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     plan.close()
+
+
+def _edge_workload(H, W, D, C, tilt, dtype, seed):
+    """Two cameras with an H x W map and D bins on a 40 x 40 grid."""
+    base = wl.ring_rig()
+    intr = base.intrinsics[:2].copy()
+    intr[:] = [0.8 * max(W, 4), 0.8 * max(W, 4), W / 2.0, H / 2.0]
+    rig = dataclasses.replace(base, n_cams=2, feat_h=H, feat_w=W, n_depth=D, depth_step=59.0 / D, nx=40, ny=40,
+                              cell_x=2.7, cell_y=2.7, intrinsics=intr, extrinsics=base.extrinsics[:2].copy())
+    if tilt:
+        rig = wl.tilt_rig(rig, tilt, 0.4 * tilt)
+    return _rig_workload(rig, C, seed=seed, batch=2, dtype=dtype)
+
+
+@pytest.mark.parametrize("H,W,D,C,tilt,dtype", [
+    (16, 4, 16, 16, 0.0, "f32"),      # one whole tile and step
+    (1, 1, 1, 4, 0.0, "f32"),         # the smallest
+    (17, 5, 15, 20, 3.0, "f32"),      # one past a tile, one short of a step
+    (15, 3, 17, 84, 8.0, "bf16"),     # one short of a tile, many slots per bin
+    (33, 8, 70, 112, 8.0, "f16"),     # 7 channel tiles run as 8
+    (48, 6, 33, 128, 20.0, "f32"),    # the widest slice, W even and not a multiple of 4
+    (31, 12, 40, 132, 5.0, "f32"),    # two slices, the second adds to dP
+    (20, 7, 300, 96, 1.0, "bf16"),    # 6 tiles, odd W, lists of several steps per wave
+    (16, 4, 1100, 8, 6.0, "f32"),     # more bins than are placed at a time
+])
+def test_backward_tile_edges(torch_cuda, pkg, oracle_lib, H, W, D, C, tilt, dtype):
+    """The matrix-core kernel at the edges of its tiles, steps and slices."""
+    _say(f"[backward edges] H={H} W={W} D={D} C={C} tilt={tilt} {dtype}")
+    w = _edge_workload(H, W, D, C, tilt, dtype, seed=40)
+    _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 41), dtype=dtype)
