@@ -125,6 +125,19 @@ template <int NCH>
 constexpr int slot_stride() { return 16 * NCH + ((NCH % 2 == 0) ? 16 : 0); }
 
 
+// Row segments that end inside the row loop (SEG) go to a queue of the lane
+// group in LDS, which is stored after the loop, or before a row that could
+// overfill it (a row ends at most kColDepth segments of a group). The code for
+// the end of a segment appears once per depth bin and row of the unrolled loop,
+// so it has to be short: with the stores and the mean's divisions in it the
+// kernel was 64 KB, the whole instruction cache of two CUs, and the stores also
+// took the place of the stages' loads in flight (loads and stores complete in
+// order on one counter). Groups start on different bank quarters.
+template <int NCH>
+constexpr int queue_rows() { return NCH <= 5 ? 12 : 9; }
+template <int NCH>
+constexpr int queue_stride() { return queue_rows<NCH>() * 16 * NCH + 16; }
+
 // Column items in (camera, column block, depth block) order are placed so
 // that consecutive depth blocks of one column block share an XCD's L2 and,
 // three at a time, a CU's L1 (xcd_cu_remap in device.h).
@@ -241,7 +254,7 @@ int zero_blocks(const ZeroArgs &z) { return (z.zero_end - z.zero_begin + BS - 1)
 
 template <int DT, int NCH, bool VEC, bool MAXR, bool SEG>
 __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0, int cn,
-                            float *s_pb) {
+                            float *s_pb, float *s_queue, int2 *s_qrow) {
     constexpr uint32_t ES = Elem<DT>::kBytes;
     const int db = item % a.items_d;
     const int t = item / a.items_d;
@@ -276,6 +289,15 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
     const int64_t tab0 = (int64_t(n) * a.D + d) * a.W + w;
     int2 e = make_int2(-1, 0);
     if (dw_ok) e = a.table[tab0];
+    // (the other planes' entries with it, before the stages: behind them the
+    // prologue would wait for every stage's loads. Lanes and planes without
+    // an entry read a valid one.)
+    int2 eqs[SEG ? kMaxSeg : 1];
+    if constexpr (SEG) {
+#pragma unroll
+        for (int q = 1; q < kMaxSeg; ++q)
+            eqs[q] = a.table[int64_t(min(q, a.n_planes - 1)) * a.plane + (dw_ok ? tab0 : 0)];
+    }
     Stage<NCH> st[kStages];
     // Issued stage by stage, in the order in which the loop consumes them:
     // the loop's waits count outstanding loads in issue order, and a
@@ -315,8 +337,10 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
     // of the table. One sweep over the rows serves them all: a lane masks
     // its probability to the segment that holds its row, and when the rows
     // pass the end of a segment that is not its combo's last, the depth
-    // bin's sums go to that segment's row and start again from zero. The
-    // last segment is emitted after the loop like a whole combo.
+    // bin's sums go to the group's queue for that segment's row and start
+    // again from zero. The last segment is emitted after the loop like a whole
+    // combo. (1-degree rig, bf16: 33.7 -> 26.6 us, four slabs 25.0 -> 20.6 us
+    // against stores at the end of each segment.)
     // A segment whose cell is gathered (demoted to a generic cell) has no
     // entry: the list is compacted to the served segments, whose rows the
     // sweep masks and flushes; rows of the others stay masked.
@@ -328,8 +352,7 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
         for (int q = 1; q < kMaxSeg; ++q) seg[q] = make_int2(-1, 0);
 #pragma unroll
         for (int q = 1; q < kMaxSeg; ++q) {
-            const int2 eq = (dw_ok && q < a.n_planes) ? a.table[int64_t(q) * a.plane + tab0]
-                                                      : make_int2(-1, 0);
+            const int2 eq = (dw_ok && q < a.n_planes) ? eqs[q] : make_int2(-1, 0);
             if (eq.x >= 0) {
 #pragma unroll
                 for (int i = 0; i < kMaxSeg; ++i) seg[i] = i == nseg ? eq : seg[i];
@@ -337,28 +360,21 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
             }
         }
     }
-    // the lane's current segment for masking, and the next segment to flush
-    int cur = 0, fl = 0;
-    auto seg_lo = [&](int q) {
-        int v = 0;
-#pragma unroll
-        for (int i = 0; i < (SEG ? kMaxSeg : 1); ++i) v = i == q ? int(uint32_t(seg[i].y) & 0xFFFFu) : v;
-        return v;
-    };
-    auto seg_hi = [&](int q) {
-        int v = 0;
-#pragma unroll
-        for (int i = 0; i < (SEG ? kMaxSeg : 1); ++i) v = i == q ? int((uint32_t(seg[i].y) >> 16) & 0x3FFFu) : v;
-        return v;
-    };
+    // segment q of the lane's combo
     auto seg_entry = [&](int q) {
         int2 v = make_int2(-1, 0);
 #pragma unroll
         for (int i = 0; i < (SEG ? kMaxSeg : 1); ++i) v = i == q ? seg[i] : v;
         return v;
     };
-    // row after which segment fl ends, if it is not the last one
-    auto flush_row = [&]() { return fl + 1 < nseg ? seg_hi(fl) - 1 : 0x7FFFFFFF; };
+    auto lo_of = [](int2 e) { return int(uint32_t(e.y) & 0xFFFFu); };
+    auto hi_of = [](int2 e) { return int((uint32_t(e.y) >> 16) & 0x3FFFu); };
+    // the lane's current segment for masking with its rows, and the next
+    // segment to flush with the row that it ends with (none for the last one)
+    constexpr int kNever = 0x7FFFFFFF;
+    int cur = 0, cur_lo = lo_of(seg[0]), cur_hi = hi_of(seg[0]);
+    int fl = 0, fl_end = nseg > 1 ? hi_of(seg[0]) - 1 : kNever;
+    int n_queued = 0;                             // of this lane group
     const bool act = nseg > 0;
     // the whole combo's rows (one plane)
     const uint32_t ey0 = uint32_t(e.y);
@@ -376,31 +392,59 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
     const float masked = MAXR ? __builtin_nanf("") : 0.f;   // probability of a row outside the combo
     const bool mean = !MAXR && a.mean != 0;
 
-    // depth bin J's sums to the row of its segment that ends at row r, if
-    // one does (lane J of the group knows), then from zero again
+    float *queue = s_queue + wl * queue_stride<NCH>() + j;
+    int2 *qrow = s_qrow + wl * queue_rows<NCH>();
+    // the queued segments to their rows
+    auto drain = [&]() {
+        __builtin_amdgcn_wave_barrier();
+        for (int i = 0; __ballot(i < n_queued) != 0; ++i) {
+            const bool has = i < n_queued;
+            const int at = has ? i : 0;
+            const int2 qe = qrow[at];
+            float v[NCH];
+#pragma unroll
+            for (int k = 0; k < NCH; ++k) v[k] = queue[at * 16 * NCH + 16 * k];
+            if (mean && !(uint32_t(qe.y) & kComboMulti)) {
+                const float cnt = float(hi_of(qe) - lo_of(qe));
+#pragma unroll
+                for (int k = 0; k < NCH; ++k) v[k] = v[k] / cnt;
+            }
+            store_row<NCH, VEC>(fr.O, has ? uint32_t(qe.x) * uint32_t(a.ldo) * 4u + uint32_t(c0) * 4u : kOff, v, tail_ok);
+        }
+        n_queued = 0;
+        __builtin_amdgcn_wave_barrier();
+    };
+    // depth bin J's sums to the queue when its segment ends at row r (lane J of
+    // the group knows), then from zero again. The wave's depth bins that end
+    // here are scalar bits, so the others cost a scalar branch each; a group
+    // whose own bin does not end keeps its sums.
     auto flush = [&](int r) {
-        const int my = flush_row();
+        const bool mine = fl_end == r;
+        const uint64_t ends = __ballot(mine);
+        if (ends == 0) return;
+        if (__ballot(n_queued + kColDepth > queue_rows<NCH>())) drain();
+        const uint32_t jm = uint32_t(ends | (ends >> 16) | (ends >> 32) | (ends >> 48)) & 0xFFu;
+        const int2 fe = seg_entry(fl);
+        const int fx = mine ? fe.x : -1;
         static_for<0, kColDepth>([&](auto Jc) {
             constexpr int J = decltype(Jc)::value;
-            if (row_bcast<J>(my) == r) {
-                const int2 fe = seg_entry(fl);
-                const int x = row_bcast<J>(fe.x);
-                const uint32_t y = uint32_t(row_bcast<J>(fe.y));
-                float v[NCH];
+            if (jm & (1u << J)) {
+                const int x = row_bcast<J>(fx), y = row_bcast<J>(fe.y);
+                if (x >= 0) {
 #pragma unroll
-                for (int k = 0; k < NCH; ++k) v[k] = acc[J][k];
-                if (mean && !(y & kComboMulti)) {
-                    const float cnt = float(int((y >> 16) & 0x3FFFu) - int(y & 0xFFFFu));
-#pragma unroll
-                    for (int k = 0; k < NCH; ++k) v[k] = v[k] / cnt;
+                    for (int k = 0; k < NCH; ++k) {
+                        queue[n_queued * 16 * NCH + 16 * k] = acc[J][k];
+                        acc[J][k] = MAXR ? -INFINITY : 0.f;
+                    }
+                    qrow[n_queued] = make_int2(x, y);
+                    ++n_queued;
                 }
-                store_row<NCH, VEC>(fr.O, x >= 0 ? uint32_t(x) * uint32_t(a.ldo) * 4u + uint32_t(c0) * 4u : kOff,
-                                    v, tail_ok);
-#pragma unroll
-                for (int k = 0; k < NCH; ++k) acc[J][k] = MAXR ? -INFINITY : 0.f;
             }
         });
-        if (my == r) ++fl;
+        if (mine) {
+            ++fl;
+            fl_end = fl + 1 < nseg ? hi_of(seg_entry(fl)) - 1 : kNever;
+        }
     };
 
     if (dm != 0) {
@@ -419,8 +463,13 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
                 const int hp = hs + hsel;
                 bool keep;
                 if constexpr (SEG) {
-                    while (cur + 1 < nseg && hp >= seg_hi(cur)) ++cur;
-                    keep = hp >= seg_lo(cur) && hp < seg_hi(cur);
+                    while (__ballot(cur + 1 < nseg && hp >= cur_hi)) {
+                        if (cur + 1 < nseg && hp >= cur_hi) ++cur;
+                        const int2 ec = seg_entry(cur);
+                        cur_lo = lo_of(ec);
+                        cur_hi = hi_of(ec);
+                    }
+                    keep = hp >= cur_lo && hp < cur_hi;
                 } else {
                     keep = hp >= hlo && hp < hhi;
                 }
@@ -432,7 +481,7 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
                 const float4 r1b = *reinterpret_cast<const float4 *>(pq + 12);
                 __builtin_amdgcn_wave_barrier();
                 // a segment of some lane's combo ends in this stage
-                const bool split = SEG && __ballot(flush_row() <= hs + 1) != 0;
+                const bool split = SEG && __ballot(fl_end <= hs + 1) != 0;
                 apply_row<NCH, MAXR>(acc, r0a, r0b, st[u].f0);
                 if (split) flush(hs);
                 apply_row<NCH, MAXR>(acc, r1a, r1b, st[u].f1);
@@ -442,8 +491,10 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
         }
     }
 
-    // the combo's last segment (the whole combo when it has one)
+    // the queued segments, then the combo's last segment (the whole combo
+    // when it has one)
     if constexpr (SEG) {
+        drain();
         const int2 el = seg_entry(nseg > 0 ? nseg - 1 : 0);
         Emit<0, NCH, VEC>::run(acc, el.x, el.y, dm, fr.O, uint32_t(c0) * 4u, a.ldo, mean, tail_ok);
     } else {
@@ -579,6 +630,8 @@ __global__ __launch_bounds__(kFwdBlock) void k_forward(FwdArgs a) {
     __shared__ float s_part[kColWidth * slot_stride<NCH>()];   // heavy cells: group partials
     __shared__ int s_cell[kFwdBlock];                          // zero rows: cell ids
     __shared__ __align__(16) float s_pb[kFwdBlock];   // probability broadcast: 16 words per lane group
+    __shared__ float s_queue[SEG ? kColWidth * queue_stride<NCH>() : 1];   // segments that ended
+    __shared__ int2 s_qrow[SEG ? kColWidth * queue_rows<NCH>() : 1];
     const int bx = blockIdx.x, b = blockIdx.y;
     const int c0 = blockIdx.z * a.slice_c;
     const int cn = min(a.slice_c, a.C - c0);
@@ -588,7 +641,7 @@ __global__ __launch_bounds__(kFwdBlock) void k_forward(FwdArgs a) {
         return;  // padding: column items start on a multiple of 8
     } else if (bx < a.base_col + a.n_items) {
         column_item<DT, NCH, VEC, MAXR, SEG>(a, Frame(a, b), xcd_cu_remap<kCuRounds>(bx - a.base_col, a.n_items),
-                                        c0, cn, s_pb);
+                                        c0, cn, s_pb, s_queue, s_qrow);
     } else if (bx < a.base_zero) {
         return;
     } else if (bx < a.base_light) {

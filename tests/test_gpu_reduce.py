@@ -300,3 +300,40 @@ def test_slab_backward(torch_cuda, pkg, oracle_lib):
     errF = np.abs(gf.cpu().numpy().reshape(rig.n_pixels, C).astype(np.float64) - refF.reshape(rig.n_pixels, C))
     assert (errF <= 1e-4 * np.sqrt(np.maximum(k, 1))[:, None]).all(), errF.max()
     sp.close()
+
+
+def _segment_rig():
+    """One camera, 33 x 9 pixels, 20 bins, tilted so that combos have up to
+    four row segments and a column's eight bins up to 18 segments that end
+    inside the row loop: more than a lane group's queue holds."""
+    base = wl.ring_rig()
+    intr = base.intrinsics[:1].copy()
+    intr[:] = [10.8, 10.8, 4.5, 16.5]
+    rig = dataclasses.replace(base, n_cams=1, feat_h=33, feat_w=9, n_depth=20, depth_min=10.0, depth_step=2.0,
+                              nx=180, ny=180, cell_x=0.6, cell_y=0.6, intrinsics=intr,
+                              extrinsics=base.extrinsics[:1].copy())
+    return wl.tilt_rig(rig, 2.0, 0.8)
+
+
+@pytest.mark.parametrize("mode", ["sum", "mean", "max"])
+@pytest.mark.parametrize("C,dtype", [(5, "f32"), (80, "f32"), (80, "bf16"), (100, "f16"), (128, "f32"), (136, "f32")])
+def test_segment_queue(torch_cuda, pkg, oracle_lib, C, dtype, mode):
+    _say(f"[segments] C={C} {dtype} {mode}")
+    torch = torch_cuda
+    rig = _segment_rig()
+    Pd, Fd, Ph, Fh = _inputs(torch, rig, C, seed=17, dtype=dtype, batch=2)
+    plan = pkg.Plan.from_rig(rig)
+    assert plan.info.n_planes == 4 and plan.info.n_generic == 0
+    out = torch.full((2, rig.ny, rig.nx, C), float("nan"), device="cuda")
+    plan.forward(Pd, Fd, out=out, reduce=mode)
+    torch.cuda.synchronize()
+    cop = oracle_lib.cell_map(rig)
+    n = _counts(oracle_lib, rig, cop)
+    if mode == "sum":
+        ref = oracle_lib.pool(rig, cop, Ph, Fh).reshape(out.shape)
+        err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
+        assert (err <= 1e-4 * np.sqrt(np.maximum(n, 1))[None, :, :, None]).all()
+    else:
+        ref = oracle_lib.pool_reduce(rig, cop, Ph, Fh, mode)
+        _check_reduce(out.cpu().numpy(), ref, n, mode)
+    plan.close()
