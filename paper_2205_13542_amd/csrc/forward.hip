@@ -125,7 +125,11 @@ template <int NCH>
 constexpr int slot_stride() { return 16 * NCH + ((NCH % 2 == 0) ? 16 : 0); }
 
 
-// Row segments that end inside the row loop (SEG) go to a queue of the lane
+// How a column item serves combos of several row segments: not at all (one
+// plane), storing each segment where it ends, or through the queue below.
+constexpr int kOnePlane = 0, kStored = 1, kQueued = 2;
+
+// Row segments that end inside the row loop (kQueued) go to a queue of the lane
 // group in LDS, which is stored after the loop, or before a row that could
 // overfill it (a row ends at most kColDepth segments of a group). The code for
 // the end of a segment appears once per depth bin and row of the unrolled loop,
@@ -133,8 +137,17 @@ constexpr int slot_stride() { return 16 * NCH + ((NCH % 2 == 0) ? 16 : 0); }
 // kernel was 64 KB, the whole instruction cache of two CUs, and the stores also
 // took the place of the stages' loads in flight (loads and stores complete in
 // order on one counter). Groups start on different bank quarters.
+//
+// The queue leaves a CU four workgroups at 80 channels where registers alone
+// allow six to eight, so it is for calls whose column items are all resident
+// with it and that gather no cells (80 channels, 1-degree rig, one bf16 frame:
+// 54.6 -> 47.3 us with the layout copy). Beyond that the stored form is faster:
+// four frames 105 against 114 us, and the gathered cells beside the items wait
+// for loads at half the waves (2-degree rig, 60 against 80 us; 3-degree rig, 92
+// against 126 us; 128 channels, 1-degree rig, 42 against 58 us).
+constexpr int kQueueChunks = 5;    // 16-channel chunks of a row, at most
 template <int NCH>
-constexpr int queue_rows() { return NCH <= 5 ? 12 : 9; }
+constexpr int queue_rows() { return 12; }
 template <int NCH>
 constexpr int queue_stride() { return queue_rows<NCH>() * 16 * NCH + 16; }
 
@@ -252,7 +265,7 @@ __device__ __forceinline__ void static_for(Fn &&fn) {
 template <int BS>
 int zero_blocks(const ZeroArgs &z) { return (z.zero_end - z.zero_begin + BS - 1) / BS; }
 
-template <int DT, int NCH, bool VEC, bool MAXR, bool SEG>
+template <int DT, int NCH, bool VEC, bool MAXR, int SEG>
 __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0, int cn,
                             float *s_pb, float *s_queue, int2 *s_qrow) {
     constexpr uint32_t ES = Elem<DT>::kBytes;
@@ -292,8 +305,8 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
     // (the other planes' entries with it, before the stages: behind them the
     // prologue would wait for every stage's loads. Lanes and planes without
     // an entry read a valid one.)
-    int2 eqs[SEG ? kMaxSeg : 1];
-    if constexpr (SEG) {
+    int2 eqs[SEG != kOnePlane ? kMaxSeg : 1];
+    if constexpr (SEG != kOnePlane) {
 #pragma unroll
         for (int q = 1; q < kMaxSeg; ++q)
             eqs[q] = a.table[int64_t(min(q, a.n_planes - 1)) * a.plane + (dw_ok ? tab0 : 0)];
@@ -337,17 +350,17 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
     // of the table. One sweep over the rows serves them all: a lane masks
     // its probability to the segment that holds its row, and when the rows
     // pass the end of a segment that is not its combo's last, the depth
-    // bin's sums go to the group's queue for that segment's row and start
+    // bin's sums go to that segment's row (or the group's queue for it) and start
     // again from zero. The last segment is emitted after the loop like a whole
     // combo. (1-degree rig, bf16: 33.7 -> 26.6 us, four slabs 25.0 -> 20.6 us
     // against stores at the end of each segment.)
     // A segment whose cell is gathered (demoted to a generic cell) has no
     // entry: the list is compacted to the served segments, whose rows the
     // sweep masks and flushes; rows of the others stay masked.
-    int2 seg[SEG ? kMaxSeg : 1];
+    int2 seg[SEG != kOnePlane ? kMaxSeg : 1];
     int nseg = e.x >= 0 ? 1 : 0;
     seg[0] = e;
-    if constexpr (SEG) {
+    if constexpr (SEG != kOnePlane) {
 #pragma unroll
         for (int q = 1; q < kMaxSeg; ++q) seg[q] = make_int2(-1, 0);
 #pragma unroll
@@ -364,7 +377,7 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
     auto seg_entry = [&](int q) {
         int2 v = make_int2(-1, 0);
 #pragma unroll
-        for (int i = 0; i < (SEG ? kMaxSeg : 1); ++i) v = i == q ? seg[i] : v;
+        for (int i = 0; i < (SEG != kOnePlane ? kMaxSeg : 1); ++i) v = i == q ? seg[i] : v;
         return v;
     };
     auto lo_of = [](int2 e) { return int(uint32_t(e.y) & 0xFFFFu); };
@@ -414,7 +427,7 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
         n_queued = 0;
         __builtin_amdgcn_wave_barrier();
     };
-    // depth bin J's sums to the queue when its segment ends at row r (lane J of
+    // depth bin J's sums to the queue (or, stored, to its row) when its segment ends at row r (lane J of
     // the group knows), then from zero again. The wave's depth bins that end
     // here are scalar bits, so the others cost a scalar branch each; a group
     // whose own bin does not end keeps its sums.
@@ -422,6 +435,33 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
         const bool mine = fl_end == r;
         const uint64_t ends = __ballot(mine);
         if (ends == 0) return;
+        if constexpr (SEG == kStored) {
+            const int2 fe = seg_entry(fl);
+            static_for<0, kColDepth>([&](auto Jc) {
+                constexpr int J = decltype(Jc)::value;
+                if (row_bcast<J>(int(mine))) {
+                    const int x = row_bcast<J>(fe.x);
+                    const uint32_t y = uint32_t(row_bcast<J>(fe.y));
+                    float v[NCH];
+#pragma unroll
+                    for (int k = 0; k < NCH; ++k) v[k] = acc[J][k];
+                    if (mean && !(y & kComboMulti)) {
+                        const float cnt = float(int((y >> 16) & 0x3FFFu) - int(y & 0xFFFFu));
+#pragma unroll
+                        for (int k = 0; k < NCH; ++k) v[k] = v[k] / cnt;
+                    }
+                    store_row<NCH, VEC>(fr.O, x >= 0 ? uint32_t(x) * uint32_t(a.ldo) * 4u + uint32_t(c0) * 4u : kOff,
+                                        v, tail_ok);
+#pragma unroll
+                    for (int k = 0; k < NCH; ++k) acc[J][k] = MAXR ? -INFINITY : 0.f;
+                }
+            });
+            if (mine) {
+                ++fl;
+                fl_end = fl + 1 < nseg ? hi_of(seg_entry(fl)) - 1 : kNever;
+            }
+            return;
+        }
         if (__ballot(n_queued + kColDepth > queue_rows<NCH>())) drain();
         const uint32_t jm = uint32_t(ends | (ends >> 16) | (ends >> 32) | (ends >> 48)) & 0xFFu;
         const int2 fe = seg_entry(fl);
@@ -462,7 +502,7 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
                 const int hs = h + 2 * u;
                 const int hp = hs + hsel;
                 bool keep;
-                if constexpr (SEG) {
+                if constexpr (SEG != kOnePlane) {
                     while (__ballot(cur + 1 < nseg && hp >= cur_hi)) {
                         if (cur + 1 < nseg && hp >= cur_hi) ++cur;
                         const int2 ec = seg_entry(cur);
@@ -481,7 +521,7 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
                 const float4 r1b = *reinterpret_cast<const float4 *>(pq + 12);
                 __builtin_amdgcn_wave_barrier();
                 // a segment of some lane's combo ends in this stage
-                const bool split = SEG && __ballot(fl_end <= hs + 1) != 0;
+                const bool split = SEG != kOnePlane && __ballot(fl_end <= hs + 1) != 0;
                 apply_row<NCH, MAXR>(acc, r0a, r0b, st[u].f0);
                 if (split) flush(hs);
                 apply_row<NCH, MAXR>(acc, r1a, r1b, st[u].f1);
@@ -493,8 +533,8 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
 
     // the queued segments, then the combo's last segment (the whole combo
     // when it has one)
-    if constexpr (SEG) {
-        drain();
+    if constexpr (SEG != kOnePlane) {
+        if constexpr (SEG == kQueued) drain();
         const int2 el = seg_entry(nseg > 0 ? nseg - 1 : 0);
         Emit<0, NCH, VEC>::run(acc, el.x, el.y, dm, fr.O, uint32_t(c0) * 4u, a.ldo, mean, tail_ok);
     } else {
@@ -625,18 +665,18 @@ __device__ void heavy_generic(const FwdArgs &a, const Frame &fr, int k, int c0, 
     }
 }
 
-template <int DT, int NCH, bool VEC, bool MAXR, bool SEG>
+template <int DT, int NCH, bool VEC, bool MAXR, int SEG>
 __global__ __launch_bounds__(kFwdBlock) void k_forward(FwdArgs a) {
     __shared__ float s_part[kColWidth * slot_stride<NCH>()];   // heavy cells: group partials
     __shared__ int s_cell[kFwdBlock];                          // zero rows: cell ids
     __shared__ __align__(16) float s_pb[kFwdBlock];   // probability broadcast: 16 words per lane group
-    __shared__ float s_queue[SEG ? kColWidth * queue_stride<NCH>() : 1];   // segments that ended
-    __shared__ int2 s_qrow[SEG ? kColWidth * queue_rows<NCH>() : 1];
+    __shared__ float s_queue[SEG == kQueued ? kColWidth * queue_stride<NCH>() : 1];   // segments that ended
+    __shared__ int2 s_qrow[SEG == kQueued ? kColWidth * queue_rows<NCH>() : 1];
     const int bx = blockIdx.x, b = blockIdx.y;
     const int c0 = blockIdx.z * a.slice_c;
     const int cn = min(a.slice_c, a.C - c0);
     if (bx < a.n_heavy) {
-        heavy_generic<DT, NCH, VEC, MAXR>(a, Frame(a, b), bx, c0, cn, s_part);
+        if constexpr (SEG != kQueued) heavy_generic<DT, NCH, VEC, MAXR>(a, Frame(a, b), bx, c0, cn, s_part);
     } else if (bx < a.base_col) {
         return;  // padding: column items start on a multiple of 8
     } else if (bx < a.base_col + a.n_items) {
@@ -646,7 +686,7 @@ __global__ __launch_bounds__(kFwdBlock) void k_forward(FwdArgs a) {
         return;
     } else if (bx < a.base_light) {
         if (blockIdx.z == 0) zero_rows<kFwdBlock>(a.zero, bx - a.base_zero, b, s_cell);   // whole rows
-    } else {
+    } else if constexpr (SEG != kQueued) {   // (calls with gathered cells are never queued)
         const int k = (bx - a.base_light) * kFwdWaves + int(threadIdx.x >> 6);
         if (k < a.n_light) light_generic<DT, NCH, VEC, MAXR>(a, Frame(a, b), k, c0, cn);
     }
@@ -778,9 +818,23 @@ __global__ __launch_bounds__(kBlock) void k_combine(CombineArgs a) {
     }
 }
 
+// Rows of more than kQueueChunks chunks.
+template <int DT, bool MAXR, int SEG>
+void launch_wide(const FwdArgs &a, dim3 grid, int nch, bool vec, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const dim3 block(kFwdBlock);
+    switch (nch) {
+        case 6: hipExtLaunchKernelGGL((k_forward<DT, 6, false, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a); break;
+        case 7: hipExtLaunchKernelGGL((k_forward<DT, 7, false, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a); break;
+        default:
+            if (vec) hipExtLaunchKernelGGL((k_forward<DT, 8, true, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a);
+            else hipExtLaunchKernelGGL((k_forward<DT, 8, false, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a);
+            break;
+    }
+}
+
 // Kernel-boundary events (either may be null): they take the timestamps of
 // the dispatch itself rather than of separate queue entries.
-template <int DT, bool MAXR, bool SEG>
+template <int DT, bool MAXR, int SEG>
 void launch_dtype(const FwdArgs &a, dim3 grid, int nch, bool vec, hipStream_t s, hipEvent_t e0,
                   hipEvent_t e1) {
     const dim3 block(kFwdBlock);
@@ -796,16 +850,20 @@ void launch_dtype(const FwdArgs &a, dim3 grid, int nch, bool vec, hipStream_t s,
             if (vec) hipExtLaunchKernelGGL((k_forward<DT, 5, true, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a);
             else hipExtLaunchKernelGGL((k_forward<DT, 5, false, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a);
             break;
-        case 6: hipExtLaunchKernelGGL((k_forward<DT, 6, false, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a); break;
-        case 7: hipExtLaunchKernelGGL((k_forward<DT, 7, false, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a); break;
         default:
-            if (vec) hipExtLaunchKernelGGL((k_forward<DT, 8, true, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a);
-            else hipExtLaunchKernelGGL((k_forward<DT, 8, false, MAXR, SEG>), grid, block, 0, s, e0, e1, 0, a);
+            if constexpr (SEG != kQueued) launch_wide<DT, MAXR, SEG>(a, grid, nch, vec, s, e0, e1);
             break;
     }
 }
 
-template <bool MAXR, bool SEG>
+// Workgroups of the queued form that a CU holds: by its LDS, 160 KB.
+int queued_per_cu(int nch) {
+    const int rows = queue_rows<kQueueChunks>();
+    const int bytes = kColWidth * ((rows * 16 * nch + 16) * 4 + rows * 8) + 8 * kFwdBlock;
+    return 160 * 1024 / bytes;
+}
+
+template <bool MAXR, int SEG>
 void launch_forward(const FwdArgs &a, int dtype, dim3 grid, int nch, bool vec, hipStream_t s,
                     hipEvent_t e0, hipEvent_t e1) {
     switch (dtype) {
@@ -929,11 +987,17 @@ int bevpool_launch_forward(const void *P, const void *F, const bevpool_plan_s *p
                                  (nch == 8 && slice_c == 128 && channels % 128 == 0));
     const bool maxr = reduce == BEVPOOL_MAX;
     hipEvent_t fstop = combine ? nullptr : stop;
-    const bool seg = a.n_planes > 1;   // some combos split into row segments: several passes
-    if (maxr && seg) launch_forward<true, true>(a, dtype, grid, nch, vec, stream, start, fstop);
-    else if (maxr) launch_forward<true, false>(a, dtype, grid, nch, vec, stream, start, fstop);
-    else if (seg) launch_forward<false, true>(a, dtype, grid, nch, vec, stream, start, fstop);
-    else launch_forward<false, false>(a, dtype, grid, nch, vec, stream, start, fstop);
+    const bool seg = a.n_planes > 1;   // some combos split into row segments
+    // the queue: no gathered cells, and every column item resident at once
+    constexpr int kCus = 256;
+    const bool queued = seg && plan->n_generic == 0 && nch <= kQueueChunks &&
+                        int64_t(a.n_items) * batch * n_slices <= int64_t(kCus) * queued_per_cu(nch);
+    if (maxr && queued) launch_forward<true, kQueued>(a, dtype, grid, nch, vec, stream, start, fstop);
+    else if (maxr && seg) launch_forward<true, kStored>(a, dtype, grid, nch, vec, stream, start, fstop);
+    else if (maxr) launch_forward<true, kOnePlane>(a, dtype, grid, nch, vec, stream, start, fstop);
+    else if (queued) launch_forward<false, kQueued>(a, dtype, grid, nch, vec, stream, start, fstop);
+    else if (seg) launch_forward<false, kStored>(a, dtype, grid, nch, vec, stream, start, fstop);
+    else launch_forward<false, kOnePlane>(a, dtype, grid, nch, vec, stream, start, fstop);
     BEVPOOL_HIP(hipGetLastError());
     if (combine) {
         CombineArgs ca;
