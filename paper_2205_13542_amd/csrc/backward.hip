@@ -368,6 +368,26 @@ __device__ __forceinline__ void end_slot(Slot &t, bool ok) {
     t.m = ok ? t.m : make_int4(0, 0, 0, 0);
 }
 
+// One dF value over the points of its own pixel. The matrix product adds 0 x G
+// of the slots that do not hold the row, which is not 0 for an infinity or a
+// NaN: a sum that is not finite is formed again by this, so that only pixels
+// with a point in such a cell see it (mixed precision meets infinities when the
+// loss scale is too large). Off the usual path: a comparison per value there.
+template <int DT>
+__device__ __forceinline__ float kept_sum(const MmaArgs &a, Rsrc P, Rsrc G, int s0, int s1, int n, int i, int h, int w, int c) {
+    float v = 0.f;
+    for (int k = s0; k < s1; ++k) {
+        const int4 m = a.masks[k], cell = a.cells[k];
+        const int bits = (i < 2 ? m.x : m.y) >> (i % 2 * 16 + h % kMRows);
+        if (!(bits & 1)) continue;
+        const int to = i == 0 ? cell.x : i == 1 ? cell.y : i == 2 ? cell.z : cell.w;
+        const uint32_t pt = (uint32_t(n * a.D + a.bins[k]) * uint32_t(a.H) + uint32_t(h)) * uint32_t(a.W) + uint32_t(w);
+        const float g = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(G, int((uint32_t(to) * uint32_t(a.C) + uint32_t(c)) * 4u), 0, 0));
+        v = __builtin_fmaf(Elem<DT>::load(P, pt * uint32_t(Elem<DT>::kBytes)), g, v);
+    }
+    return v;
+}
+
 template <int DT, int T, bool WIDE>
 __global__ __launch_bounds__(kMBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_backward_mma(MmaArgs a) {
@@ -622,6 +642,7 @@ void k_backward_mma(MmaArgs a) {
             for (int u = 0; u < kMWaves; ++u) v += s_all[u * 2 * kSum + x * kWaveSize + lane];
             const int i = x / (4 * T), t = x % (4 * T) / 4, h = h0 + 4 * q + x % 4, w = w0 + i0 + i;
             const bool ok = (h < a.H) & (w < a.W) & (16 * t + j < a.cn);
+            if (ok && !(fabsf(v) <= 3.402823466e+38f)) v = kept_sum<DT>(a, P, G, s0, s1, n, i0 + i, h, w, a.c0 + 16 * t + j);
             const uint32_t row = (uint32_t(n) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w)) * uint32_t(a.C);
             store_f32(dF, ok ? (row + uint32_t(a.c0 + 16 * t + j)) * 4u : kOff, v);
         }

@@ -298,3 +298,36 @@ def test_backward_tile_edges(torch_cuda, pkg, oracle_lib, H, W, D, C, tilt, dtyp
     _say(f"[backward edges] H={H} W={W} D={D} C={C} tilt={tilt} {dtype}")
     w = _edge_workload(H, W, D, C, tilt, dtype, seed=40)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 41), dtype=dtype)
+
+
+@pytest.mark.parametrize("C,tilt,dtype", [(20, 0.0, "f32"), (80, 1.0, "bf16"), (132, 8.0, "f32")])
+def test_backward_non_finite_gradients(torch_cuda, pkg, oracle_lib, C, tilt, dtype):
+    """Infinities and NaN in the gradients of a few cells reach the pixels with
+    a point in such a cell and no others (sums of other pixels stay finite)."""
+    _say(f"[backward non-finite] C={C} tilt={tilt} {dtype}")
+    torch = torch_cuda
+    w = _edge_workload(33, 8, 40, C, tilt, dtype, seed=50)
+    rig = w.rig
+    cop = oracle_lib.cell_map(rig)
+    G = _grad(w, 51)
+    cells = np.random.default_rng(52).choice(np.unique(cop[cop >= 0]), 4, replace=False)
+    rows = G.reshape(w.batch, -1, C)
+    rows[:, cells[0], 0] = np.inf
+    rows[0, cells[1], C - 1] = -np.inf
+    rows[1, cells[2], :] = np.nan
+    rows[0, cells[3], C // 2] = np.inf
+    plan = pkg.Plan.from_rig(rig)
+    gd, gf = plan.backward(torch.from_numpy(G).cuda(), _dev(torch, w.P, dtype), _dev(torch, w.F, dtype))
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        refP, refF = oracle_lib.backward(rig, cop, _host_values(torch, w.P, dtype), _host_values(torch, w.F, dtype), G)
+    k = (cop >= 0).reshape(rig.n_cams, rig.n_depth, -1).sum(axis=1).reshape(-1)
+    for got, ref, bound in ((gd, refP, 1e-4 * np.sqrt(C)),
+                            (gf, refF, 1e-4 * np.sqrt(np.maximum(k, 1))[None, :, None])):
+        got = got.cpu().numpy().astype(np.float64).reshape((w.batch, -1) if got is gd else (w.batch, rig.n_pixels, C))
+        ref = ref.reshape(got.shape)
+        fin = np.isfinite(ref)
+        assert not fin.all()
+        assert (np.isfinite(got) == fin).all()
+        assert (np.where(fin, np.abs(got - np.where(fin, ref, 0.0)), 0.0) <= bound).all()
+    plan.close()
