@@ -27,8 +27,10 @@
 // memory accesses (the matrix cores alone 4.4); the rest is L1 and L2 time of
 // gathered rows and of P and dP, whose lanes each touch a line of their own. A
 // 4-column tile touches half the lines of a 2-column one, and 128 channels in
-// one launch read P once: 236 bins x 64 x 176, C = 128 went from 359 us (two
-// launches of the 2-column kernel) to 177 us, two bf16 frames of cameras tilted
+// one launch read P once: a training step of 236 bins x 64 x 176, C = 128 went
+// from 514 us (two launches of the 2-column kernel) to 336 us, and to 344 us with
+// a dP product in two sums (one sum of 128 products rounds worse: 2.0e-7 against
+// 1.5e-7 from exact), two bf16 frames of cameras tilted
 // by 1 degree from 147 us (the kernel below) to 65 us. 8 waves per workgroup:
 // 29.6 against 23.8 us; three waves per SIMD by spilling: no gain.
 //
@@ -523,13 +525,15 @@ void k_backward_mma(MmaArgs a) {
 #pragma unroll
         for (int i = 0; i < kMCols; ++i) {
             accp[i] = f4v{0.f, 0.f, 0.f, 0.f};
+            f4v part = accp[i];
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 const f4v f = s_f[(i * kMRows + j) * kFq + 4 * t + q];
+                f4v &to = t < 5 ? accp[i] : part;   // sums of at most 80 products, for their rounding
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    accp[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], g[t][e], accp[i], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) to = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], g[t][e], to, 0, 0, 0);
             }
+            if constexpr (T > 5) accp[i] += part;
             // the rows into the wave's LDS; their registers then take the
             // next column's rows, which arrive while the dF product runs
 #pragma unroll
