@@ -670,7 +670,7 @@ __device__ __forceinline__ void load_bwd_tile(const BwdListArgs &a, int32_t x, B
     const int32_t *src = a.cell_of_point + (int64_t(xb) * a.H + h0) * a.W + w0;
     // rows and columns past the map read clamped, so that all loads are
     // issued together; a row's piece is one 16-byte load where the rows keep
-    // the alignment (cell_of_point is an allocation of its own)
+    // the alignment (cell_of_point begins at a multiple of 256 bytes)
     if (a.W % kBwdCols == 0) {
 #pragma unroll
         for (int r = 0; r < kBwdRows; ++r) {
