@@ -61,6 +61,46 @@
 namespace bevpool {
 namespace {
 
+__device__ __forceinline__ bool finite(float v) { return fabsf(v) <= 3.402823466e+38f; }
+
+// dF of one pixel over its own points, for a lane group: v[t] is channel
+// c0 + 16t + j in lane j. The kernels below add 0 x G of cells that do not hold
+// the row's point, which is not 0 for an infinity or a NaN: a row with a sum
+// that is not finite is formed again by this, so that only pixels with a point
+// in such a cell see it (mixed precision meets infinities when the loss scale
+// is too large). 16 depth bins at a time, one in each lane, then their rows.
+template <int DT, int T>
+__device__ __forceinline__ void kept_row(float (&v)[T], Rsrc P, Rsrc G, const int32_t *cop, int n, int D, int H, int W,
+                                         int C, int h, int w, bool in, int c0, int cn, int j) {
+    constexpr int kRows = 4;                   // gradient rows in flight
+    const int base = int(threadIdx.x) & 48;    // the group's first lane
+#pragma unroll
+    for (int t = 0; t < T; ++t) v[t] = 0.f;
+    for (int d0 = 0; d0 < D; d0 += 16) {
+        const uint32_t pt = (uint32_t(n * D + d0 + j) * uint32_t(H) + uint32_t(h)) * uint32_t(W) + uint32_t(w);
+        const int cell = in && d0 + j < D ? cop[pt] : -1;
+        const float p = Elem<DT>::load(P, cell >= 0 ? pt * uint32_t(Elem<DT>::kBytes) : kOff);
+        for (int u0 = 0; u0 < 16; u0 += kRows) {
+            float g[kRows][T];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int c = __shfl(cell, base | (u0 + u));
+                const uint32_t row = uint32_t(max(c, 0)) * uint32_t(C) + uint32_t(c0 + j);
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    g[u][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        G, int(c >= 0 && 16 * t + j < cn ? (row + uint32_t(16 * t)) * 4u : kOff), 0, 0));
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const float pu = __shfl(p, base | (u0 + u));
+#pragma unroll
+                for (int t = 0; t < T; ++t) v[t] = __builtin_fmaf(pu, g[u][t], v[t]);
+            }
+        }
+    }
+}
+
 constexpr int kBRows = 8;                      // pixel rows per lane group
 constexpr int kBCols = 4;                      // pixel columns per workgroup (lane groups of a wave)
 constexpr int kBWaves = 4;                     // depth parts per workgroup
@@ -340,6 +380,7 @@ struct MmaArgs {
     const char *P, *F;
     const float *G;
     float *dP, *dF;
+    const int32_t *cop;
     const int32_t *offs, *bins;                // the plan's backward lists
     const int4 *cells, *masks;
     int32_t D, H, W, C, c0, cn;                // channel slice [c0, c0 + cn), cn a multiple of 4
@@ -368,26 +409,6 @@ struct Slot {
 __device__ __forceinline__ void end_slot(Slot &t, bool ok) {
     t.c = ok ? t.c : make_int4(-1, -1, -1, -1);
     t.m = ok ? t.m : make_int4(0, 0, 0, 0);
-}
-
-// One dF value over the points of its own pixel. The matrix product adds 0 x G
-// of the slots that do not hold the row, which is not 0 for an infinity or a
-// NaN: a sum that is not finite is formed again by this, so that only pixels
-// with a point in such a cell see it (mixed precision meets infinities when the
-// loss scale is too large). Off the usual path: a comparison per value there.
-template <int DT>
-__device__ __forceinline__ float kept_sum(const MmaArgs &a, Rsrc P, Rsrc G, int s0, int s1, int n, int i, int h, int w, int c) {
-    float v = 0.f;
-    for (int k = s0; k < s1; ++k) {
-        const int4 m = a.masks[k], cell = a.cells[k];
-        const int bits = (i < 2 ? m.x : m.y) >> (i % 2 * 16 + h % kMRows);
-        if (!(bits & 1)) continue;
-        const int to = i == 0 ? cell.x : i == 1 ? cell.y : i == 2 ? cell.z : cell.w;
-        const uint32_t pt = (uint32_t(n * a.D + a.bins[k]) * uint32_t(a.H) + uint32_t(h)) * uint32_t(a.W) + uint32_t(w);
-        const float g = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(G, int((uint32_t(to) * uint32_t(a.C) + uint32_t(c)) * 4u), 0, 0));
-        v = __builtin_fmaf(Elem<DT>::load(P, pt * uint32_t(Elem<DT>::kBytes)), g, v);
-    }
-    return v;
 }
 
 template <int DT, int T, bool WIDE>
@@ -627,8 +648,9 @@ void k_backward_mma(MmaArgs a) {
     }
 
     if (!a.want_df) return;
-    // two columns' sums of all waves in LDS, added in wave order; the waves
-    // take their (column, channel tile, row) values in turn
+    // two columns' sums of all waves in LDS, added in wave order: wave r takes
+    // value r of every lane, so that its lane group q holds all channels of row
+    // 4q + r
 #pragma unroll
     for (int i0 = 0; i0 < kMCols; i0 += 2) {
         __syncthreads();
@@ -640,15 +662,30 @@ void k_backward_mma(MmaArgs a) {
                 for (int r = 0; r < 4; ++r)
                     s_all[(wave * 2 + i) * kSum + (t * 4 + r) * kWaveSize + lane] = accf[i0 + i][t][r];
         __syncthreads();
-        for (int x = wave; x < 8 * T; x += kMWaves) {
-            float v = 0.f;
+        const int h = h0 + 4 * q + wave;
+#pragma unroll 1
+        for (int i = 0; i < 2; ++i) {
+            const int w = w0 + i0 + i;
+            const bool in = (h < a.H) & (w < a.W);
+            float v[T];
+            int bad = 0;
 #pragma unroll
-            for (int u = 0; u < kMWaves; ++u) v += s_all[u * 2 * kSum + x * kWaveSize + lane];
-            const int i = x / (4 * T), t = x % (4 * T) / 4, h = h0 + 4 * q + x % 4, w = w0 + i0 + i;
-            const bool ok = (h < a.H) & (w < a.W) & (16 * t + j < a.cn);
-            if (ok && !(fabsf(v) <= 3.402823466e+38f)) v = kept_sum<DT>(a, P, G, s0, s1, n, i0 + i, h, w, a.c0 + 16 * t + j);
-            const uint32_t row = (uint32_t(n) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w)) * uint32_t(a.C);
-            store_f32(dF, ok ? (row + uint32_t(a.c0 + 16 * t + j)) * 4u : kOff, v);
+            for (int t = 0; t < T; ++t) {
+                v[t] = 0.f;
+#pragma unroll
+                for (int u = 0; u < kMWaves; ++u) v[t] += s_all[(u * 2 + i) * kSum + (t * 4 + wave) * kWaveSize + lane];
+                bad |= in && !finite(v[t]) ? 1 << t : 0;
+            }
+            if (__ballot(bad != 0) != 0) {
+                // (a group without one runs along: its rows are not taken)
+                float x[T];
+                kept_row<DT, T>(x, P, G, a.cop, n, a.D, a.H, a.W, a.C, h, w, in, a.c0, a.cn, j);
+#pragma unroll
+                for (int t = 0; t < T; ++t) v[t] = bad >> t & 1 ? x[t] : v[t];
+            }
+            const uint32_t row = (uint32_t(n) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w)) * uint32_t(a.C) + uint32_t(a.c0 + j);
+#pragma unroll
+            for (int t = 0; t < T; ++t) store_f32(dF, in && 16 * t + j < a.cn ? (row + uint32_t(16 * t)) * 4u : kOff, v[t]);
         }
     }
 }
@@ -726,6 +763,7 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
         m.G = G;
         m.dP = dP;
         m.dF = dF;
+        m.cop = plan->cell_of_point;
         m.offs = plan->bwd_offs;
         m.bins = plan->bwd_bins;
         m.cells = plan->bwd_cells;

@@ -331,3 +331,42 @@ def test_backward_non_finite_gradients(torch_cuda, pkg, oracle_lib, C, tilt, dty
         assert (np.isfinite(got) == fin).all()
         assert (np.where(fin, np.abs(got - np.where(fin, ref, 0.0)), 0.0) <= bound).all()
     plan.close()
+
+
+def _call_us(torch, fn, calls=20):
+    """Median over five of the GPU's time for a call among others."""
+    fn()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / calls)
+    return sorted(times)[2]
+
+
+@pytest.mark.parametrize("C", [80, 128])
+def test_backward_infinite_gradient(torch_cuda, pkg, C):
+    """A gradient that is infinite everywhere (a loss scale too large) reaches
+    every kept point and every pixel with one, and costs one walk over the points
+    of each pixel: measured 3.5 times a finite one's time, asserted at most 12 (a
+    walk for each value took 33)."""
+    torch = torch_cuda
+    w = _rig_workload(wl.ring_rig(), C, seed=60)
+    plan = pkg.Plan.from_rig(w.rig)
+    P, F = _dev(torch, w.P, "f32"), _dev(torch, w.F, "f32")
+    G = torch.from_numpy(_grad(w, 61)).cuda()
+    inf = torch.full_like(G, float("inf"))
+    gd, gf = plan.backward(inf, P, F)
+    kept = (torch.from_numpy(plan.export()[0]) >= 0).cuda().reshape(w.rig.n_cams, w.rig.n_depth, -1)
+    assert torch.equal(~gd.reshape(kept.shape).isfinite(), kept)
+    pixels = kept.any(1).reshape(-1)
+    assert torch.equal(~gf.reshape(-1, C).isfinite(), pixels[:, None].expand(-1, C))
+    assert (gf.reshape(-1, C)[~pixels] == 0).all()
+    finite, infinite = (_call_us(torch, lambda: plan.backward(g, P, F)) for g in (G, inf))
+    _say(f"[backward infinite] C={C}: finite {finite:.1f} us, infinite {infinite:.1f} us")
+    assert infinite <= 12.0 * finite
+    plan.close()
