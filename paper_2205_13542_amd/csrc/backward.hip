@@ -5,12 +5,13 @@
 //   dF[b][pixel]  = sum over the kept points p of the pixel of P[b][p] G[b][cell(p)]
 //
 // k_backward_mma (feature and gradient rows of whole, aligned 4-element quads)
-// runs both on the matrix cores (v_mfma_f32_16x16x4f32, fp32 in and out). A
-// workgroup owns 4 adjacent columns and 16 rows of one camera. The plan lists
-// for it, in depth order, slots of one cell for each column with a mask of the
-// rows whose points lie in that cell: one slot for a depth bin of a level
-// camera, several where a tilted camera's rows cross cells. For one column and
-// the gradient rows G[s] of its slots' cells, with M the masks,
+// runs both on the matrix cores (v_mfma_f32_16x16x4f32, fp32 in and out). The
+// plan lists for 4 adjacent columns and 16 rows of one camera, in depth order,
+// slots of one cell for each column with a mask of the rows whose points lie in
+// that cell: one slot for a depth bin of a level camera, several where a tilted
+// camera's rows cross cells. A workgroup takes all 4 columns of a list, or 2
+// (four_columns below). For one column and the gradient rows G[s] of its slots'
+// cells, with M the masks,
 //   dF[h][c] = sum_s M[s][h] P[d(s)][h] G[s][c]
 //   dP[d(s)][h] = sum_c G[s][c] F[h][c]   where M[s][h] is set
 // The workgroup's four waves take consecutive parts of the list, 16 slots per
@@ -18,21 +19,22 @@
 // 16t + 4q + e (t the tile, q the lane quarter, e the element), so that F and G
 // arrive as 16-byte quads; the first takes the slots as K and reads the step's
 // gradient rows back transposed from the wave's own LDS copy. P and dP of the
-// four columns move as 16-byte pieces (8 for 16-bit P). A bin's slots lie in one
-// step, so the step's dP rows are whole and are stored once. The waves' dF sums
-// are added in LDS in wave order.
+// columns move as one piece where the map's width is a multiple of theirs. A
+// bin's slots lie in one step, so the step's dP rows are whole and are stored
+// once. The waves' dF sums are added in LDS in wave order. Both forms add in the
+// same order: their results are the same bits.
 //
-// What bounds it (fp32, 6 cameras x 118 bins x 32 x 88, C = 80, in cache): 25 us,
-// of which 8 are the kernel without its steps and 10 the steps without their
-// memory accesses (the matrix cores alone 4.4); the rest is L1 and L2 time of
-// gathered rows and of P and dP, whose lanes each touch a line of their own. A
-// 4-column tile touches half the lines of a 2-column one, and 128 channels in
-// one launch read P once: a training step of 236 bins x 64 x 176, C = 128 went
-// from 514 us (two launches of the 2-column kernel) to 336 us, and to 344 us with
-// a dP product in two sums (one sum of 128 products rounds worse: 2.0e-7 against
-// 1.5e-7 from exact), two bf16 frames of cameras tilted
-// by 1 degree from 147 us (the kernel below) to 65 us. 8 waves per workgroup:
-// 29.6 against 23.8 us; three waves per SIMD by spilling: no gain.
+// What bounds it: gathered rows and P and dP, whose lanes each touch a line of
+// their own, through L1 and L2; the matrix cores alone take 4.4 of the 24 us of 6
+// cameras x 118 bins x 32 x 88, C = 80, level, fp32, in cache. There the loads in
+// flight count: two columns at three waves per SIMD take 22.8 us, four at two
+// 24.4; cameras tilted by 1 degree 31 and 36 us, by 5 degrees 49 and 61 us (the
+// kernel below: 57 us in the last two, 84 us in 16 bits). 128 channels in one
+// launch read P once (236 bins x 64 x 176: 322 us in two launches of 80 and 48
+// channels, 165 us in one), with a dP product in two sums: one of 128 products
+// rounds worse, 2.0e-7 against 1.5e-7 from exact. Tried and no faster: 8 waves
+// per workgroup; three waves per SIMD with four columns, by spilling; the next
+// two columns' rows in flight; two columns' products interleaved.
 //
 // k_backward (other rows): pixel-stationary work on the vector ALUs. A
 // workgroup owns kBCols pixel columns x kBRows rows of one camera, and its
@@ -368,11 +370,10 @@ __global__ __launch_bounds__(kBBlock) void k_backward(BwdArgs a) {
 
 constexpr int kMWaves = 4;                     // parts of a list per workgroup
 constexpr int kMBlock = kMWaves * kWaveSize;
-constexpr int kMCols = kBwdCols;               // adjacent pixel columns per workgroup
 constexpr int kMRows = kBwdRows;               // pixel rows per workgroup (M of the instruction)
-constexpr int kMChunk = kBwdStep;               // slots per step (N of the dP product)
+constexpr int kMChunk = kBwdStep;              // slots per step (N of the dP product)
 constexpr int kMSlice = 128;                   // channels per launch, at most
-static_assert(kMCols == 4 && kMRows == 16 && kMChunk == 16, "the shape of the slots and of the instruction");
+static_assert(kBwdCols == 4 && kMRows == 16 && kMChunk == 16, "the shape of the slots and of the instruction");
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
@@ -394,46 +395,80 @@ struct MmaArgs {
 template <int T>
 constexpr int mma_stride() { return 16 * (T | 1); }
 
-// LDS words from one bin of a step's dP to the next: kMRows x kMCols values,
-// and a quad so that bins start in different banks.
-constexpr int kDpStride = kMRows * kMCols + 4;
+// V consecutive elements as fp32.
+template <int DT, int V>
+__device__ __forceinline__ void load_piece(Rsrc r, uint32_t off, float *v) {
+    if constexpr (V == 4) {
+        Elem<DT>::load4(r, off, v);
+    } else if constexpr (V == 2 && DT == BEVPOOL_F32) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b64(r, int(off), 0, 0);
+        v[0] = __uint_as_float(x[0]);
+        v[1] = __uint_as_float(x[1]);
+    } else if constexpr (V == 2) {
+        const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(r, int(off), 0, 0);
+        if constexpr (DT == BEVPOOL_BF16) {
+            v[0] = __uint_as_float(x << 16);
+            v[1] = __uint_as_float(x & 0xFFFF0000u);
+        } else {
+            v[0] = float(__builtin_bit_cast(_Float16, uint16_t(x & 0xFFFFu)));
+            v[1] = float(__builtin_bit_cast(_Float16, uint16_t(x >> 16)));
+        }
+    } else {
+        v[0] = Elem<DT>::load(r, off);
+    }
+}
 
-// Slot k + j of a list in lane (q, j): the columns' cells, row masks and bin.
-// Past the wave's last slot it holds that slot, which takes part in nothing
-// once end_slot has run.
+// Slot k + j of a list in lane (q, j): the cells, row masks (two columns to a
+// word: kept rows, rows whose dP it writes) and bin. Past the wave's last slot
+// it holds that slot, which takes part in nothing once end_slot has run.
+template <int COLS>
 struct Slot {
-    int4 c, m;
+    int c[COLS], keep[COLS / 2], write[COLS / 2];
     int d;
 };
 
-__device__ __forceinline__ void end_slot(Slot &t, bool ok) {
-    t.c = ok ? t.c : make_int4(-1, -1, -1, -1);
-    t.m = ok ? t.m : make_int4(0, 0, 0, 0);
+template <int COLS>
+__device__ __forceinline__ void end_slot(Slot<COLS> &t, bool ok) {
+#pragma unroll
+    for (int i = 0; i < COLS; ++i) t.c[i] = ok ? t.c[i] : -1;
+#pragma unroll
+    for (int i = 0; i < COLS / 2; ++i) {
+        t.keep[i] = ok ? t.keep[i] : 0;
+        t.write[i] = ok ? t.write[i] : 0;
+    }
 }
 
-template <int DT, int T, bool WIDE>
-__global__ __launch_bounds__(kMBlock) __attribute__((amdgpu_waves_per_eu(2)))
+template <int DT, int T, int COLS, int V>
+__global__ __launch_bounds__(kMBlock) __attribute__((amdgpu_waves_per_eu(COLS == 2 && T <= 5 ? 3 : 2)))
 void k_backward_mma(MmaArgs a) {
+    static_assert(COLS % V == 0 && kBwdCols % COLS == 0, "whole pieces and parts of a list's columns");
     constexpr int S = mma_stride<T>();
     constexpr int kFq = 4 * T + 1;             // quads per feature row in LDS (odd: no bank conflicts)
     constexpr int kSum = T * 4 * kWaveSize;    // one wave's dF sums of a column
+    // LDS words from one bin of a step's dP to the next: kMRows x COLS values,
+    // and a quad so that bins start in different banks
+    constexpr int kDpStride = kMRows * COLS + 4;
     constexpr int kGs = kMChunk * S > kMChunk * kDpStride ? kMChunk * S : kMChunk * kDpStride;
     constexpr uint32_t ES = Elem<DT>::kBytes;
-    // feature rows and the waves' step buffers; for the sums at the end, two
-    // columns of every wave
-    constexpr int kLds = kMCols * kMRows * kFq * 4 + kMWaves * kGs;
-    static_assert(2 * kMWaves * kSum <= kLds, "two columns' sums fit");
+    // feature rows and the waves' step buffers; for the sums at the end, one
+    // or two columns of every wave
+    constexpr int kLds = COLS * kMRows * kFq * 4 + kMWaves * kGs;
+    constexpr int kSumCols = 2 * kMWaves * kSum <= kLds ? 2 : 1;
+    static_assert(kSumCols * kMWaves * kSum <= kLds, "the columns' sums fit");
     __shared__ __attribute__((aligned(16))) float s_all[kLds];
     f4v *s_f = reinterpret_cast<f4v *>(s_all);
-    float *s_g = s_all + kMCols * kMRows * kFq * 4;
+    float *s_g = s_all + COLS * kMRows * kFq * 4;
     const int b = blockIdx.y;
-    // the row blocks of a column quad share its gradient rows: two of them on
-    // one CU; neighbouring quads share P lines: placed on one XCD
+    // the row blocks of a list's columns share its gradient rows: two of them on
+    // one CU; neighbouring columns share P lines: placed on one XCD
     const int item = xcd_cu_remap<2>(blockIdx.x, gridDim.x);
     const int rb = item % a.blocks_h;
     const int tt = item / a.blocks_h;
-    const int cq = tt % a.quads_w, n = tt / a.quads_w;
-    const int w0 = cq * kMCols, h0 = rb * kMRows;
+    constexpr int kParts = kBwdCols / COLS;    // workgroups of a list, by columns
+    const int sub = tt % kParts, cq = tt / kParts % a.quads_w, n = tt / kParts / a.quads_w;
+    const int list = tt / kParts * a.blocks_h + rb;
+    const int w0 = cq * kBwdCols + sub * COLS, h0 = rb * kMRows;
+    if (kParts > 1 && w0 >= a.W) return;       // a part past the map
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int q = lane >> 4, j = lane & 15;
 
@@ -445,14 +480,30 @@ void k_backward_mma(MmaArgs a) {
     const uint32_t HW = uint32_t(a.H) * uint32_t(a.W);
 
     // this wave's slots of the list
-    const int s0 = a.offs[item], s1 = a.offs[item + 1];
+    const int s0 = a.offs[list], s1 = a.offs[list + 1];
     const int part = ((s1 - s0 + kMWaves - 1) / kMWaves + kMChunk - 1) / kMChunk * kMChunk;
     const int lo = min(s1, s0 + wave * part), hi = min(s1, lo + part);
     // (clamped and masked later: no branch and no wait at the loads)
-    auto load_slot = [&](Slot &t, int k) {
+    auto load_slot = [&](Slot<COLS> &t, int k) {
         const int at = min(k + j, hi - 1);
-        t.c = a.cells[at];
-        t.m = a.masks[at];
+        if constexpr (COLS == 4) {
+            const int4 c = a.cells[at], m = a.masks[at];
+            t.c[0] = c.x;
+            t.c[1] = c.y;
+            t.c[2] = c.z;
+            t.c[3] = c.w;
+            t.keep[0] = m.x;
+            t.keep[1] = m.y;
+            t.write[0] = m.z;
+            t.write[1] = m.w;
+        } else {
+            const int2 c = reinterpret_cast<const int2 *>(a.cells)[int64_t(at) * 2 + sub];
+            const int32_t *m = reinterpret_cast<const int32_t *>(a.masks) + int64_t(at) * 4 + sub;
+            t.c[0] = c.x;
+            t.c[1] = c.y;
+            t.keep[0] = m[0];
+            t.write[0] = m[2];
+        }
         t.d = a.bins[at];
     };
     // the gradient rows of a column's 16 slots, slot j's row in the lanes
@@ -470,35 +521,35 @@ void k_backward_mma(MmaArgs a) {
     // the feature rows of the workgroup's columns and rows go to LDS: quad
     // 4t + q of row (i, r) holds channels c0 + 16t + 4q .. + 3. All of a
     // thread's loads are issued before the first is waited for.
-    constexpr int kQuads = kMCols * kMRows * 4 * T;
+    constexpr int kQuads = COLS * kMRows * 4 * T;
     constexpr int kFill = (kQuads + kMBlock - 1) / (kMBlock);
     float fill[kFill][4];
 #pragma unroll
     for (int u = 0; u < kFill; ++u) {
         const int x = threadIdx.x + u * kMBlock;
-        const int qd = x % (4 * T), i = (x / (4 * T)) % kMCols, r = x / (4 * T * kMCols);
+        const int qd = x % (4 * T), i = (x / (4 * T)) % COLS, r = x / (4 * T * COLS);
         const bool ok = (h0 + r < a.H) & (w0 + i < a.W) & (4 * qd < a.cn);
         const uint32_t addr = ((uint32_t(n) * HW + uint32_t(h0 + r) * uint32_t(a.W) + uint32_t(w0 + i)) * uint32_t(a.C) +
                                uint32_t(a.c0 + 4 * qd)) * ES;
         Elem<DT>::load4(F, ok ? addr : kOff, fill[u]);
     }
-    Slot sl;
+    Slot<COLS> sl;
     if (lo < hi) {
         load_slot(sl, lo);
         end_slot(sl, lo + j < hi);
-        load_rows(sl.c.x);
+        load_rows(sl.c[0]);
     }
 #pragma unroll
     for (int u = 0; u < kFill; ++u) {
         const int x = threadIdx.x + u * kMBlock;
-        const int qd = x % (4 * T), i = (x / (4 * T)) % kMCols, r = x / (4 * T * kMCols);
+        const int qd = x % (4 * T), i = (x / (4 * T)) % COLS, r = x / (4 * T * COLS);
         if (x < kQuads) s_f[(i * kMRows + r) * kFq + qd] = f4v{fill[u][0], fill[u][1], fill[u][2], fill[u][3]};
     }
 
     // dF sums: lane (q, j), value r holds row h0 + 4q + r, channel c0 + 16t + j
-    f4v accf[kMCols][T];
+    f4v accf[COLS][T];
 #pragma unroll
-    for (int i = 0; i < kMCols; ++i)
+    for (int i = 0; i < COLS; ++i)
 #pragma unroll
         for (int t = 0; t < T; ++t) accf[i][t] = f4v{0.f, 0.f, 0.f, 0.f};
     float *sg = s_g + wave * kGs;
@@ -512,29 +563,28 @@ void k_backward_mma(MmaArgs a) {
     __syncthreads();   // the feature rows are in LDS
 
     // P of slot 4s + q, row h0 + j (operand A of the dF product) where the
-    // slot's cells keep that point: bit 4s + i of kept for column i
-    float p[4][kMCols];
+    // slot's cells keep that point: bit COLS * s + i of kept for column i
+    float p[4][COLS];
     int kept = 0;
-    auto load_probs = [&](const Slot &t) {
+    auto load_probs = [&](const Slot<COLS> &t) {
         kept = 0;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const int k01 = __shfl(t.m.x, 4 * s + q) >> j, k23 = __shfl(t.m.y, 4 * s + q) >> j;
-            const int d = __shfl(t.d, 4 * s + q);
-            const int m = (k01 & 1) | (k01 >> 15 & 2) | (k23 & 1) << 2 | (k23 >> 13 & 8);
-            const uint32_t pt = (uint32_t(n * a.D + d) * uint32_t(a.H) + uint32_t(h0 + j)) * uint32_t(a.W) + uint32_t(w0);
-            if constexpr (WIDE) {
-                const uint32_t off = pt * ES;
-                Elem<DT>::load4(P, m != 0 ? off : kOff, p[s]);
-            } else {
+            int m = 0;
 #pragma unroll
-                for (int i = 0; i < kMCols; ++i)
-                    p[s][i] = Elem<DT>::load(P, m >> i & 1 ? (pt + uint32_t(i)) * ES : kOff);
+            for (int i = 0; i < COLS / 2; ++i) {
+                const int k01 = __shfl(t.keep[i], 4 * s + q) >> j;
+                m |= ((k01 & 1) | (k01 >> 15 & 2)) << (2 * i);
             }
-            kept |= m << (4 * s);
+            const int d = __shfl(t.d, 4 * s + q);
+            const uint32_t pt = (uint32_t(n * a.D + d) * uint32_t(a.H) + uint32_t(h0 + j)) * uint32_t(a.W) + uint32_t(w0);
+#pragma unroll
+            for (int i = 0; i < COLS; i += V)
+                load_piece<DT, V>(P, (m >> i & ((1 << V) - 1)) != 0 ? (pt + uint32_t(i)) * ES : kOff, &p[s][i]);
+            kept |= m << (COLS * s);
         }
     };
-    Slot next;
+    Slot<COLS> next;
     if (lo < hi) {
         load_probs(sl);
         load_slot(next, lo + kMChunk);
@@ -542,9 +592,9 @@ void k_backward_mma(MmaArgs a) {
 
     for (int k = lo; k < hi; k += kMChunk) {
         // dP product: lane (q, j), value r is row h0 + 4q + r, slot j
-        f4v accp[kMCols];
+        f4v accp[COLS];
 #pragma unroll
-        for (int i = 0; i < kMCols; ++i) {
+        for (int i = 0; i < COLS; ++i) {
             accp[i] = f4v{0.f, 0.f, 0.f, 0.f};
             f4v part = accp[i];
 #pragma unroll
@@ -560,7 +610,7 @@ void k_backward_mma(MmaArgs a) {
 #pragma unroll
             for (int t = 0; t < T; ++t) *reinterpret_cast<f4v *>(&sg_wr[16 * t]) = g[t];
             __builtin_amdgcn_wave_barrier();
-            load_rows(i == 0 ? sl.c.y : i == 1 ? sl.c.z : i == 2 ? sl.c.w : k + kMChunk + j < hi ? next.c.x : -1);
+            load_rows(i + 1 < COLS ? sl.c[(i + 1) % COLS] : k + kMChunk + j < hi ? next.c[0] : -1);
             __builtin_amdgcn_sched_barrier(0);
             // dF product: K = slot, N = channel, kRead slots quarters' reads
             // in flight at a time
@@ -575,7 +625,7 @@ void k_backward_mma(MmaArgs a) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int s = 0; s < kRead; ++s) {
-                    const float pm = kept >> (4 * (s0 + s) + i) & 1 ? p[s0 + s][i] : 0.f;
+                    const float pm = kept >> (COLS * (s0 + s) + i) & 1 ? p[s0 + s][i] : 0.f;
 #pragma unroll
                     for (int t = 0; t < T; ++t)
                         accf[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(pm, gt[s][t], accf[i][t], 0, 0, 0);
@@ -589,55 +639,62 @@ void k_backward_mma(MmaArgs a) {
         load_probs(next);
         __builtin_amdgcn_sched_barrier(0);
         if (a.want_dp) {
-            // row h of bin d: four columns, 16 bytes where they move as one
-            auto store_dp = [&](int d, int h, bool ok, float (&v)[kMCols]) {
+            // row h of bin d: the columns, V to a piece
+            auto store_dp = [&](int d, int h, bool ok, float (&v)[COLS]) {
                 const uint32_t off = ((uint32_t(n * a.D + d) * uint32_t(a.H) + uint32_t(h)) * uint32_t(a.W) + uint32_t(w0)) * 4u;
                 if (a.accumulate_dp) {
 #pragma unroll
-                    for (int i = 0; i < kMCols; ++i)
-                        v[i] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dP, int(ok & (w0 + i < a.W) ? off + 4u * i : kOff), 0, 0));
+                    for (int i = 0; i < COLS; ++i)
+                        v[i] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dP, int((ok & (w0 + i < a.W)) ? off + 4u * i : kOff), 0, 0));
                 }
-                if constexpr (WIDE) {
-                    __builtin_amdgcn_raw_buffer_store_b128(
-                        (__attribute__((ext_vector_type(4))) uint32_t){__float_as_uint(v[0]), __float_as_uint(v[1]),
-                                                                       __float_as_uint(v[2]), __float_as_uint(v[3])},
-                        dP, int(ok ? off : kOff), 0, 0);
-                } else {
 #pragma unroll
-                    for (int i = 0; i < kMCols; ++i) store_f32(dP, ok & (w0 + i < a.W) ? off + 4u * i : kOff, v[i]);
+                for (int i = 0; i < COLS; i += V) {
+                    const int at = int((ok & (w0 + i < a.W)) ? off + 4u * i : kOff);
+                    if constexpr (V == 4)
+                        __builtin_amdgcn_raw_buffer_store_b128(
+                            (__attribute__((ext_vector_type(4))) uint32_t){__float_as_uint(v[0]), __float_as_uint(v[1]),
+                                                                           __float_as_uint(v[2]), __float_as_uint(v[3])},
+                            dP, at, 0, 0);
+                    else if constexpr (V == 2)
+                        __builtin_amdgcn_raw_buffer_store_b64(
+                            (__attribute__((ext_vector_type(2))) uint32_t){__float_as_uint(v[i]), __float_as_uint(v[i + 1])},
+                            dP, at, 0, 0);
+                    else
+                        store_f32(dP, uint32_t(at), v[i]);
                 }
             };
             const bool real = k + j < hi;
             const int d0 = __builtin_amdgcn_readfirstlane(sl.d);
+            // bit of column i and the lane's row r in a word of masks
+            auto bit = [&](const int (&m)[COLS / 2], int i, int r) { return (m[i / 2] >> (4 * q + r + i % 2 * 16) & 1) != 0; };
             if (__ballot(real & (sl.d != d0 + j)) == 0) {
                 // every bin of the step has one slot
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int k01 = sl.m.x >> (4 * q + r), k23 = sl.m.y >> (4 * q + r);
-                    float v[kMCols] = {k01 & 1 ? accp[0][r] : 0.f, k01 & 0x10000 ? accp[1][r] : 0.f,
-                                       k23 & 1 ? accp[2][r] : 0.f, k23 & 0x10000 ? accp[3][r] : 0.f};
+                    float v[COLS];
+#pragma unroll
+                    for (int i = 0; i < COLS; ++i) v[i] = bit(sl.keep, i, r) ? accp[i][r] : 0.f;
                     store_dp(sl.d, h0 + 4 * q + r, real & (h0 + 4 * q + r < a.H), v);
                 }
             } else {
                 // the slots' values meet in LDS (a bin's slots lie in one
                 // step), so that every row of a bin is stored once
-                float *mine = sg + (sl.d - d0) * kDpStride + 4 * q * kMCols;
+                float *mine = sg + (sl.d - d0) * kDpStride + 4 * q * COLS;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int k01 = sl.m.x >> (4 * q + r), k23 = sl.m.y >> (4 * q + r);
-                    const int w01 = sl.m.z >> (4 * q + r), w23 = sl.m.w >> (4 * q + r);
-                    if (w01 & 1) mine[r * kMCols] = k01 & 1 ? accp[0][r] : 0.f;
-                    if (w01 & 0x10000) mine[r * kMCols + 1] = k01 & 0x10000 ? accp[1][r] : 0.f;
-                    if (w23 & 1) mine[r * kMCols + 2] = k23 & 1 ? accp[2][r] : 0.f;
-                    if (w23 & 0x10000) mine[r * kMCols + 3] = k23 & 0x10000 ? accp[3][r] : 0.f;
-                }
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int i = 0; i < COLS; ++i)
+                        if (bit(sl.write, i, r)) mine[r * COLS + i] = bit(sl.keep, i, r) ? accp[i][r] : 0.f;
                 __builtin_amdgcn_wave_barrier();
                 // bins of this step: up to the last real slot's
                 const int bins = __shfl(sl.d, min(hi - k, kMChunk) - 1) - d0 + 1;
                 for (int x = lane; x < bins * kMRows; x += kWaveSize) {
                     const int h = h0 + x % kMRows;
-                    const f4v u = *reinterpret_cast<const f4v *>(&sg[x / kMRows * kDpStride + x % kMRows * kMCols]);
-                    float v[kMCols] = {u[0], u[1], u[2], u[3]};
+                    typedef float fcv __attribute__((ext_vector_type(COLS)));
+                    const fcv u = *reinterpret_cast<const fcv *>(&sg[x / kMRows * kDpStride + x % kMRows * COLS]);
+                    float v[COLS];
+#pragma unroll
+                    for (int i = 0; i < COLS; ++i) v[i] = u[i];
                     store_dp(d0 + x / kMRows, h, h < a.H, v);
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -648,23 +705,23 @@ void k_backward_mma(MmaArgs a) {
     }
 
     if (!a.want_df) return;
-    // two columns' sums of all waves in LDS, added in wave order: wave r takes
-    // value r of every lane, so that its lane group q holds all channels of row
-    // 4q + r
+    // the sums of all waves in LDS, kSumCols columns at a time, added in wave
+    // order: wave r takes value r of every lane, so that its lane group q holds
+    // all channels of row 4q + r
 #pragma unroll
-    for (int i0 = 0; i0 < kMCols; i0 += 2) {
+    for (int i0 = 0; i0 < COLS; i0 += kSumCols) {
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < kSumCols; ++i)
 #pragma unroll
             for (int t = 0; t < T; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    s_all[(wave * 2 + i) * kSum + (t * 4 + r) * kWaveSize + lane] = accf[i0 + i][t][r];
+                    s_all[(wave * kSumCols + i) * kSum + (t * 4 + r) * kWaveSize + lane] = accf[i0 + i][t][r];
         __syncthreads();
         const int h = h0 + 4 * q + wave;
 #pragma unroll 1
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < kSumCols; ++i) {
             const int w = w0 + i0 + i;
             const bool in = (h < a.H) & (w < a.W);
             float v[T];
@@ -673,7 +730,7 @@ void k_backward_mma(MmaArgs a) {
             for (int t = 0; t < T; ++t) {
                 v[t] = 0.f;
 #pragma unroll
-                for (int u = 0; u < kMWaves; ++u) v[t] += s_all[(u * 2 + i) * kSum + (t * 4 + wave) * kWaveSize + lane];
+                for (int u = 0; u < kMWaves; ++u) v[t] += s_all[(u * kSumCols + i) * kSum + (t * 4 + wave) * kWaveSize + lane];
                 bad |= in && !finite(v[t]) ? 1 << t : 0;
             }
             if (__ballot(bad != 0) != 0) {
@@ -690,27 +747,52 @@ void k_backward_mma(MmaArgs a) {
     }
 }
 
-template <int DT, bool WIDE>
+template <int DT, int COLS, int V>
 void launch_mma(const MmaArgs &a, dim3 grid, int tiles, hipStream_t s) {
     const dim3 block(kMBlock);
     switch (tiles) {
-        case 1: hipLaunchKernelGGL((k_backward_mma<DT, 1, WIDE>), grid, block, 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_backward_mma<DT, 2, WIDE>), grid, block, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_backward_mma<DT, 3, WIDE>), grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((k_backward_mma<DT, 4, WIDE>), grid, block, 0, s, a); break;
-        case 5: hipLaunchKernelGGL((k_backward_mma<DT, 5, WIDE>), grid, block, 0, s, a); break;
-        case 6: hipLaunchKernelGGL((k_backward_mma<DT, 6, WIDE>), grid, block, 0, s, a); break;
-        default: hipLaunchKernelGGL((k_backward_mma<DT, 8, WIDE>), grid, block, 0, s, a); break;
+        case 1: hipLaunchKernelGGL((k_backward_mma<DT, 1, COLS, V>), grid, block, 0, s, a); break;
+        case 2: hipLaunchKernelGGL((k_backward_mma<DT, 2, COLS, V>), grid, block, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((k_backward_mma<DT, 3, COLS, V>), grid, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL((k_backward_mma<DT, 4, COLS, V>), grid, block, 0, s, a); break;
+        case 5: hipLaunchKernelGGL((k_backward_mma<DT, 5, COLS, V>), grid, block, 0, s, a); break;
+        case 6: hipLaunchKernelGGL((k_backward_mma<DT, 6, COLS, V>), grid, block, 0, s, a); break;
+        default: hipLaunchKernelGGL((k_backward_mma<DT, 8, COLS, V>), grid, block, 0, s, a); break;
     }
 }
 
-template <bool WIDE>
+template <int COLS, int V>
 void launch_mma(const MmaArgs &a, int dtype, dim3 grid, int tiles, hipStream_t s) {
     switch (dtype) {
-        case BEVPOOL_F32: launch_mma<BEVPOOL_F32, WIDE>(a, grid, tiles, s); break;
-        case BEVPOOL_BF16: launch_mma<BEVPOOL_BF16, WIDE>(a, grid, tiles, s); break;
-        default: launch_mma<BEVPOOL_F16, WIDE>(a, grid, tiles, s); break;
+        case BEVPOOL_F32: launch_mma<BEVPOOL_F32, COLS, V>(a, grid, tiles, s); break;
+        case BEVPOOL_BF16: launch_mma<BEVPOOL_BF16, COLS, V>(a, grid, tiles, s); break;
+        default: launch_mma<BEVPOOL_F16, COLS, V>(a, grid, tiles, s); break;
     }
+}
+
+// Four columns to a workgroup, or two, for `bins` depth bins of all lists and
+// frames and P and dP in pieces of `piece` columns. Four read the slots, P and dP
+// in half as many accesses, which counts once there is more to move than the
+// caches hold; two make twice the workgroups, three to a CU, and keep more loads
+// in flight, the more so where a tilted rig's bins have several slots. Times in
+// us, four against two, 32 x 88 and 118 bins unless said:
+//   80 channels, level: one camera (5 thousand bins) 14.0 / 10.4, six (31) 24.4 /
+//   22.8, two frames (62) 37.4 / 36.5, three (93) 45.8 / 50.3, eight (249) 126 /
+//   156; eight frames of 40 bins (84) 60 / 56. Tilted by 1 degree: one frame 36 /
+//   31, four (125) 91 / 84, five (156) 116 / 127.
+//   32 channels, level: 40 bins (11) 9.0 / 8.7, two frames of them (21) 12.6 / 14.0.
+//   1 degree: 31 22.4 / 21.9, 62 31.3 / 34.5.
+//   128 channels, level: 125 94 / 89, 156 113 / 117, 64 x 176 x 236 bins (249) 165 /
+//   173. 1 degree: 31 55 / 46, 249 287 / 263.
+//   87 columns (one at a time), level, 80 channels: 125 84 / 80, 249 176 / 194; 128
+//   channels: 249 254 / 225.
+// Widths of 2 mod 4 move in pairs with two columns: 50 x 28, 80 channels, eight
+// frames 65 us, one at a time with four 79.
+bool four_columns(int tiles, int64_t bins, bool level, int piece) {
+    if (piece == 2 || (tiles > 6 && (piece == 1 || !level))) return false;
+    if (piece == 1 || tiles > 6) return bins >= 150000;
+    if (tiles <= 2) return bins >= (level ? 20000 : 40000);
+    return bins >= (level ? 90000 : 150000);
 }
 
 template <int DT>
@@ -763,7 +845,6 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
         m.G = G;
         m.dP = dP;
         m.dF = dF;
-        m.cop = plan->cell_of_point;
         m.offs = plan->bwd_offs;
         m.bins = plan->bwd_bins;
         m.cells = plan->bwd_cells;
@@ -777,14 +858,18 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
         m.g_bytes = uint32_t(g_bytes);
         m.dp_bytes = dP ? uint32_t(dp_bytes) : 0u;
         m.df_bytes = dF ? uint32_t(df_bytes) : 0u;
-        m.quads_w = (g.feat_w + kMCols - 1) / kMCols;
+        m.quads_w = (g.feat_w + kBwdCols - 1) / kBwdCols;
         m.blocks_h = (g.feat_h + kMRows - 1) / kMRows;
-        // P and dP of the four columns move as one piece
-        const bool wide = g.feat_w % kMCols == 0 && reinterpret_cast<uintptr_t>(P) % (4 * esize) == 0 &&
-                          reinterpret_cast<uintptr_t>(dP) % 16 == 0;
+        m.cop = plan->cell_of_point;
         m.want_dp = dP != nullptr;
         m.want_df = dF != nullptr;
-        const dim3 grid(g.n_cams * m.quads_w * m.blocks_h, batch);
+        // v columns of P and of dP move as one piece
+        auto pieces = [&](int v) {
+            return g.feat_w % v == 0 && reinterpret_cast<uintptr_t>(P) % (v * esize) == 0 &&
+                   reinterpret_cast<uintptr_t>(dP) % (4 * v) == 0;
+        };
+        const int piece = pieces(4) ? 4 : pieces(2) ? 2 : 1;
+        const int64_t lists = int64_t(g.n_cams) * m.quads_w * m.blocks_h, bins = lists * g.n_depth;
         // equal slices of at most kMSlice channels, whole 16-channel tiles
         const int n_slices = (channels + kMSlice - 1) / kMSlice;
         const int slice = ((channels + n_slices - 1) / n_slices + 15) / 16 * 16;
@@ -793,8 +878,12 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
             m.cn = std::min(slice, channels - c0);
             m.accumulate_dp = c0 > 0;
             const int tiles = (m.cn + 15) / 16;
-            if (wide) launch_mma<true>(m, dtype, grid, tiles, stream);
-            else launch_mma<false>(m, dtype, grid, tiles, stream);
+            const bool four = four_columns(tiles, bins * batch, plan->n_bwd_slots == bins, piece);
+            const dim3 grid(uint32_t(four ? lists : 2 * lists), batch);
+            if (four && piece == 4) launch_mma<4, 4>(m, dtype, grid, tiles, stream);
+            else if (four) launch_mma<4, 1>(m, dtype, grid, tiles, stream);
+            else if (piece != 1) launch_mma<2, 2>(m, dtype, grid, tiles, stream);
+            else launch_mma<2, 1>(m, dtype, grid, tiles, stream);
             BEVPOOL_HIP(hipGetLastError());
         }
         return BEVPOOL_OK;

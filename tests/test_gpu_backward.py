@@ -270,7 +270,7 @@ def test_backward_level_deterministic(torch_cuda, pkg):
     plan.close()
 
 
-def _edge_workload(H, W, D, C, tilt, dtype, seed):
+def _edge_workload(H, W, D, C, tilt, dtype, seed, batch=2):
     """Two cameras with an H x W map and D bins on a 40 x 40 grid."""
     base = wl.ring_rig()
     intr = base.intrinsics[:2].copy()
@@ -279,7 +279,7 @@ def _edge_workload(H, W, D, C, tilt, dtype, seed):
                               cell_x=2.7, cell_y=2.7, intrinsics=intr, extrinsics=base.extrinsics[:2].copy())
     if tilt:
         rig = wl.tilt_rig(rig, tilt, 0.4 * tilt)
-    return _rig_workload(rig, C, seed=seed, batch=2, dtype=dtype)
+    return _rig_workload(rig, C, seed=seed, batch=batch, dtype=dtype)
 
 
 @pytest.mark.parametrize("H,W,D,C,tilt,dtype", [
@@ -298,6 +298,39 @@ def test_backward_tile_edges(torch_cuda, pkg, oracle_lib, H, W, D, C, tilt, dtyp
     _say(f"[backward edges] H={H} W={W} D={D} C={C} tilt={tilt} {dtype}")
     w = _edge_workload(H, W, D, C, tilt, dtype, seed=40)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 41), dtype=dtype)
+
+
+@pytest.mark.parametrize("H,W,D,C,tilt,dtype,batch", [
+    (16, 4, 1100, 20, 6.0, "f16", 19),    # 2 tiles: from 40 thousand bins of a tilted rig
+    (33, 8, 700, 80, 0.0, "f32", 11),     # 5 tiles: from 90 thousand of a level one
+    (33, 8, 1100, 132, 1.0, "f32", 12),   # slices of 5 and 4 tiles, from 150 thousand
+    (31, 12, 1100, 96, 5.0, "bf16", 12),  # 6 tiles
+    (33, 7, 1100, 68, 1.0, "f32", 12),    # odd W: columns move one by one
+])
+def test_backward_four_columns(torch_cuda, pkg, oracle_lib, H, W, D, C, tilt, dtype, batch):
+    """Enough bins over all frames that a workgroup takes four columns."""
+    _say(f"[backward four columns] H={H} W={W} D={D} C={C} tilt={tilt} {dtype} batch={batch}")
+    w = _edge_workload(H, W, D, C, tilt, dtype, seed=42, batch=batch)
+    _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 43), dtype=dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("offset", [1, 2])
+def test_backward_unaligned_probabilities(torch_cuda, pkg, dtype, offset):
+    """P one and two elements past a 16-byte boundary: columns move one by one
+    or in pairs, and the gradients are the same bits as with an aligned P."""
+    torch = torch_cuda
+    _say(f"[backward] P {offset} elements past alignment, {dtype}")
+    w = _edge_workload(17, 8, 40, 36, 3.0, dtype, seed=44)
+    plan = pkg.Plan.from_rig(w.rig)
+    P, F = _dev(torch, w.P, dtype), _dev(torch, w.F, dtype)
+    buf = torch.empty(P.numel() + offset, dtype=P.dtype, device="cuda")
+    buf[offset:] = P.reshape(-1)
+    G = torch.from_numpy(_grad(w, 45)).cuda()
+    a = plan.backward(G, P, F)
+    b = plan.backward(G, buf[offset:].view(P.shape), F)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    plan.close()
 
 
 @pytest.mark.parametrize("C,tilt,dtype", [(20, 0.0, "f32"), (80, 1.0, "bf16"), (132, 8.0, "f32")])
