@@ -65,42 +65,41 @@ namespace {
 
 __device__ __forceinline__ bool finite(float v) { return fabsf(v) <= 3.402823466e+38f; }
 
-// dF of one pixel over its own points, for a lane group: v[t] is channel
-// c0 + 16t + j in lane j. The kernels below add 0 x G of cells that do not hold
-// the row's point, which is not 0 for an infinity or a NaN: a row with a sum
-// that is not finite is formed again by this, so that only pixels with a point
-// in such a cell see it (mixed precision meets infinities when the loss scale
-// is too large). 16 depth bins at a time, one in each lane, then their rows.
-template <int DT, int T>
-__device__ __forceinline__ void kept_row(float (&v)[T], Rsrc P, Rsrc G, const int32_t *cop, int n, int D, int H, int W,
-                                         int C, int h, int w, bool in, int c0, int cn, int j) {
+// dF of one pixel over its own points, for a lane group in load_row's layout of
+// the channels from c0 on (values past the slice are not to be used). The
+// kernels below add 0 x G of cells that do not hold the row's point, which is
+// not 0 for an infinity or a NaN: a row with a sum that is not finite is formed
+// again by this, so that only pixels with a point in such a cell see it (mixed
+// precision meets infinities when the loss scale is too large). 16 depth bins at
+// a time, one in each lane, then their rows.
+template <int DT, int NCH, bool VEC>
+__device__ __forceinline__ Row<NCH> kept_row(Rsrc P, Rsrc G, const int32_t *cop, int n, int D, int H, int W, int C,
+                                             int h, int w, bool in, int c0, int j) {
     constexpr int kRows = 4;                   // gradient rows in flight
     const int base = int(threadIdx.x) & 48;    // the group's first lane
+    Row<NCH> v;
 #pragma unroll
-    for (int t = 0; t < T; ++t) v[t] = 0.f;
+    for (int k = 0; k < NCH; ++k) v.v[k] = 0.f;
     for (int d0 = 0; d0 < D; d0 += 16) {
         const uint32_t pt = (uint32_t(n * D + d0 + j) * uint32_t(H) + uint32_t(h)) * uint32_t(W) + uint32_t(w);
         const int cell = in && d0 + j < D ? cop[pt] : -1;
         const float p = Elem<DT>::load(P, cell >= 0 ? pt * uint32_t(Elem<DT>::kBytes) : kOff);
         for (int u0 = 0; u0 < 16; u0 += kRows) {
-            float g[kRows][T];
+            Row<NCH> g[kRows];
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int c = __shfl(cell, base | (u0 + u));
-                const uint32_t row = uint32_t(max(c, 0)) * uint32_t(C) + uint32_t(c0 + j);
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-                    g[u][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                        G, int(c >= 0 && 16 * t + j < cn ? (row + uint32_t(16 * t)) * 4u : kOff), 0, 0));
+                load_row<BEVPOOL_F32, NCH, VEC>(g[u], G, c >= 0 ? (uint32_t(c) * uint32_t(C) + uint32_t(c0)) * 4u : kOff);
             }
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const float pu = __shfl(p, base | (u0 + u));
 #pragma unroll
-                for (int t = 0; t < T; ++t) v[t] = __builtin_fmaf(pu, g[u][t], v[t]);
+                for (int k = 0; k < NCH; ++k) v.v[k] = __builtin_fmaf(pu, g[u].v[k], v.v[k]);
             }
         }
     }
+    return v;
 }
 
 constexpr int kBRows = 8;                      // pixel rows per lane group
@@ -153,7 +152,8 @@ __device__ __forceinline__ float transpose_reduce(const float (&v)[kBRows], int 
 }
 
 // acc[r] += pv_r * g and dot[r] = f[r] . g for the kBRows rows, pv_r from
-// lane r of the group.
+// lane r of the group. What a tail lane's last value holds lies past the slice:
+// it stays out of the dot product (its feature is 0, but 0 x infinity is not).
 template <int R, int NCH>
 struct RowTerms {
     static __device__ __forceinline__ void run(float (&acc)[kBRows][NCH], float (&dot)[kBRows],
@@ -194,7 +194,7 @@ __device__ __forceinline__ void each_loads(Row<NCH> (&g)[kBEach], Rsrc G, uint32
 template <int R0, int U, int NCH>
 __device__ __forceinline__ void each_terms(float (&acc)[kBRows][NCH], float (&dot)[kBRows],
                                            const Row<NCH> (&f)[kBRows], const Row<NCH> (&g)[kBEach],
-                                           float pv) {
+                                           float pv, bool tail_ok) {
     if constexpr (U < kBEach) {
         constexpr int R = R0 + U;
         const float p = row_bcast<R>(pv);
@@ -202,29 +202,32 @@ __device__ __forceinline__ void each_terms(float (&acc)[kBRows][NCH], float (&do
 #pragma unroll
         for (int k = 0; k < NCH; ++k) {
             acc[R][k] = __builtin_fmaf(p, g[U].v[k], acc[R][k]);
-            s = __builtin_fmaf(f[R].v[k], g[U].v[k], s);
+            const float x = __builtin_fmaf(f[R].v[k], g[U].v[k], s);
+            s = k < NCH - 1 || tail_ok ? x : s;
         }
         dot[R] = s;
-        each_terms<R0, U + 1, NCH>(acc, dot, f, g, pv);
+        each_terms<R0, U + 1, NCH>(acc, dot, f, g, pv, tail_ok);
     }
 }
 template <int R0, int NCH, bool VEC>
 __device__ __forceinline__ void row_terms_each(float (&acc)[kBRows][NCH], float (&dot)[kBRows],
                                                const Row<NCH> (&f)[kBRows], Rsrc G, uint32_t g_ch,
-                                               int C, int cell, float pv) {
+                                               int C, int cell, float pv, bool tail_ok) {
     if constexpr (R0 < kBRows) {
         Row<NCH> g[kBEach];
         each_loads<R0, 0, NCH, VEC>(g, G, g_ch, C, cell);
-        each_terms<R0, 0, NCH>(acc, dot, f, g, pv);
-        row_terms_each<R0 + kBEach, NCH, VEC>(acc, dot, f, G, g_ch, C, cell, pv);
+        each_terms<R0, 0, NCH>(acc, dot, f, g, pv, tail_ok);
+        row_terms_each<R0 + kBEach, NCH, VEC>(acc, dot, f, G, g_ch, C, cell, pv, tail_ok);
     }
 }
 
 template <int NCH>
 constexpr int bwd_stride() { return kBRows * NCH * 16 + 16; }   // one lane group's dF sums in LDS
 
+// (held to three waves per SIMD at five values a lane, which 169 registers miss)
 template <int DT, int NCH, bool VEC>
-__global__ __launch_bounds__(kBBlock) void k_backward(BwdArgs a) {
+__global__ __launch_bounds__(kBBlock) __attribute__((amdgpu_waves_per_eu(NCH == 5 ? 3 : 1)))
+void k_backward(BwdArgs a) {
     __shared__ float s_df[(kBWaves - 1) * kBCols * bwd_stride<NCH>()];
     // dP of a chunk: [wave][depth bin of the chunk][row][column]
     __shared__ float s_dp[kBWaves * kBChunk * kBRows * kBCols];
@@ -306,10 +309,11 @@ __global__ __launch_bounds__(kBBlock) void k_backward(BwdArgs a) {
                 const bool kept = st[u].cell >= 0;
                 const float pv = kept ? st[u].pv : 0.f;
                 float dot[kBRows];
+                if (!tail_ok) st[u].g.v[NCH - 1] = 0.f;
                 if (st[u].cc >= 0) {
                     RowTerms<0, NCH>::run(acc, dot, f, st[u].g, pv);
                 } else if (st[u].cc == -2) {
-                    row_terms_each<0, NCH, VEC>(acc, dot, f, G, g_ch, a.C, st[u].cell, pv);
+                    row_terms_each<0, NCH, VEC>(acc, dot, f, G, g_ch, a.C, st[u].cell, pv, tail_ok);
                 } else {
 #pragma unroll
                     for (int r = 0; r < kBRows; ++r) dot[r] = 0.f;
@@ -360,9 +364,30 @@ __global__ __launch_bounds__(kBBlock) void k_backward(BwdArgs a) {
     }
     const uint32_t df_col = in_w ? (uint32_t(n * a.HW + h0 * a.W + w) * uint32_t(a.C) + uint32_t(a.c0)) * 4u : kOff;
     const uint32_t df_row = uint32_t(a.W) * uint32_t(a.C) * 4u;
+    float zero = 0.f;                          // NaN once a sum is not finite
+#pragma unroll
+    for (int r = 0; r < kBRows; ++r) {
+        store_row<NCH, VEC>(dF, h0 + r < a.H ? df_col + uint32_t(r) * df_row : kOff, acc[r], tail_ok);
+#pragma unroll
+        for (int k = 0; k < NCH; ++k) zero = __builtin_fmaf(acc[r][k], 0.f, zero);
+    }
+    if (__ballot(zero != 0.f) == 0) return;
+    uint64_t bad = 0u;                         // bit r * NCH + k: value k of row r
 #pragma unroll
     for (int r = 0; r < kBRows; ++r)
-        store_row<NCH, VEC>(dF, h0 + r < a.H ? df_col + uint32_t(r) * df_row : kOff, acc[r], tail_ok);
+#pragma unroll
+        for (int k = 0; k < NCH; ++k)
+            bad |= !finite(acc[r][k]) && in_w && h0 + r < a.H && (k < NCH - 1 || tail_ok) ? uint64_t(1) << (r * NCH + k) : 0u;
+#pragma unroll 1
+    for (int r = 0; r < kBRows; ++r) {
+        const uint32_t mine = uint32_t(bad >> (r * NCH)) & ((1u << NCH) - 1u);
+        if (__ballot(mine != 0u) == 0) continue;
+        // (a group without one runs along)
+        const Row<NCH> x = kept_row<DT, NCH, VEC>(P, G, a.cop, n, a.D, a.H, a.W, a.C, h0 + r, w, in_w && h0 + r < a.H, a.c0, j);
+#pragma unroll
+        for (int k = 0; k < NCH; ++k)
+            store_f32(dF, mine >> k & 1u ? df_col + uint32_t(r) * df_row + uint32_t(VEC && k < 4 ? 4 * j + k : j + 16 * k) * 4u : kOff, x.v[k]);
+    }
 }
 
 
@@ -731,14 +756,13 @@ void k_backward_mma(MmaArgs a) {
                 v[t] = 0.f;
 #pragma unroll
                 for (int u = 0; u < kMWaves; ++u) v[t] += s_all[(u * kSumCols + i) * kSum + (t * 4 + wave) * kWaveSize + lane];
-                bad |= in && !finite(v[t]) ? 1 << t : 0;
+                bad |= in && 16 * t + j < a.cn && !finite(v[t]) ? 1 << t : 0;
             }
             if (__ballot(bad != 0) != 0) {
                 // (a group without one runs along: its rows are not taken)
-                float x[T];
-                kept_row<DT, T>(x, P, G, a.cop, n, a.D, a.H, a.W, a.C, h, w, in, a.c0, a.cn, j);
+                const Row<T> x = kept_row<DT, T, false>(P, G, a.cop, n, a.D, a.H, a.W, a.C, h, w, in, a.c0, j);
 #pragma unroll
-                for (int t = 0; t < T; ++t) v[t] = bad >> t & 1 ? x[t] : v[t];
+                for (int t = 0; t < T; ++t) v[t] = bad >> t & 1 ? x.v[t] : v[t];
             }
             const uint32_t row = (uint32_t(n) * HW + uint32_t(h) * uint32_t(a.W) + uint32_t(w)) * uint32_t(a.C) + uint32_t(a.c0 + j);
 #pragma unroll

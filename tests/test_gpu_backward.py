@@ -333,7 +333,10 @@ def test_backward_unaligned_probabilities(torch_cuda, pkg, dtype, offset):
     plan.close()
 
 
-@pytest.mark.parametrize("C,tilt,dtype", [(20, 0.0, "f32"), (80, 1.0, "bf16"), (132, 8.0, "f32")])
+@pytest.mark.parametrize("C,tilt,dtype", [
+    (20, 0.0, "f32"), (80, 1.0, "bf16"), (132, 8.0, "f32"),               # matrix cores
+    (5, 0.0, "f32"), (67, 0.0, "bf16"), (63, 8.0, "f16"), (90, 1.0, "f32"),   # per-row kernel
+])
 def test_backward_non_finite_gradients(torch_cuda, pkg, oracle_lib, C, tilt, dtype):
     """Infinities and NaN in the gradients of a few cells reach the pixels with
     a point in such a cell and no others (sums of other pixels stay finite)."""
@@ -381,7 +384,7 @@ def _call_us(torch, fn, calls=20):
     return sorted(times)[2]
 
 
-@pytest.mark.parametrize("C", [80, 128])
+@pytest.mark.parametrize("C", [80, 128, 67])
 def test_backward_infinite_gradient(torch_cuda, pkg, C):
     """A gradient that is infinite everywhere (a loss scale too large) reaches
     every kept point and every pixel with one, and costs one walk over the points
