@@ -39,9 +39,9 @@
 // k_backward (other rows): pixel-stationary work on the vector ALUs. A
 // workgroup owns kBCols pixel columns x kBRows rows of one camera, and its
 // kBWaves waves take consecutive parts of the depth bins. A group of 16
-// lanes owns one column; lane j holds the row slice channels (the forward's
-// lane layout) of the kBRows feature rows, read once, and the kBRows rows'
-// dF sums. For each depth bin the group reads one gradient row when the
+// lanes owns one column; lane j holds channels j, j + 16, ... of the slice of
+// the kBRows feature rows, read once, and the kBRows rows' dF sums. For each
+// depth bin the group reads one gradient row when the
 // combo (camera, depth bin, column) is clean, or one per kept row otherwise.
 // dF gets P x G; dP gets the dot product F . G, reduced across the 16 lanes
 // by a transpose-reduce (8 shuffles for the 8 rows' sums). A wave parks the
@@ -65,14 +65,14 @@ namespace {
 
 __device__ __forceinline__ bool finite(float v) { return fabsf(v) <= 3.402823466e+38f; }
 
-// dF of one pixel over its own points, for a lane group in load_row's layout of
-// the channels from c0 on (values past the slice are not to be used). The
+// dF of one pixel over its own points, for a lane group: value k of lane j is channel
+// c0 + 16k + j (past the slice: not to be used). The
 // kernels below add 0 x G of cells that do not hold the row's point, which is
 // not 0 for an infinity or a NaN: a row with a sum that is not finite is formed
 // again by this, so that only pixels with a point in such a cell see it (mixed
 // precision meets infinities when the loss scale is too large). 16 depth bins at
 // a time, one in each lane, then their rows.
-template <int DT, int NCH, bool VEC>
+template <int DT, int NCH>
 __device__ __forceinline__ Row<NCH> kept_row(Rsrc P, Rsrc G, const int32_t *cop, int n, int D, int H, int W, int C,
                                              int h, int w, bool in, int c0, int j) {
     constexpr int kRows = 4;                   // gradient rows in flight
@@ -89,7 +89,7 @@ __device__ __forceinline__ Row<NCH> kept_row(Rsrc P, Rsrc G, const int32_t *cop,
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int c = __shfl(cell, base | (u0 + u));
-                load_row<BEVPOOL_F32, NCH, VEC>(g[u], G, c >= 0 ? (uint32_t(c) * uint32_t(C) + uint32_t(c0)) * 4u : kOff);
+                load_row<BEVPOOL_F32, NCH, false>(g[u], G, c >= 0 ? (uint32_t(c) * uint32_t(C) + uint32_t(c0)) * 4u : kOff);
             }
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
@@ -182,13 +182,13 @@ struct RowTerms<kBRows, NCH> {
 // serves them (loading and using each row in turn made every row wait for
 // all loads in flight).
 constexpr int kBEach = 4;
-template <int R0, int U, int NCH, bool VEC>
+template <int R0, int U, int NCH>
 __device__ __forceinline__ void each_loads(Row<NCH> (&g)[kBEach], Rsrc G, uint32_t g_ch, int C, int cell) {
     if constexpr (U < kBEach) {
         const int c = row_bcast<R0 + U>(cell);
         const uint32_t addr = uint32_t(max(c, 0)) * uint32_t(C) * 4u + g_ch;
-        load_row<BEVPOOL_F32, NCH, VEC>(g[U], G, c >= 0 ? addr : kOff);
-        each_loads<R0, U + 1, NCH, VEC>(g, G, g_ch, C, cell);
+        load_row<BEVPOOL_F32, NCH, false>(g[U], G, c >= 0 ? addr : kOff);
+        each_loads<R0, U + 1, NCH>(g, G, g_ch, C, cell);
     }
 }
 template <int R0, int U, int NCH>
@@ -209,23 +209,23 @@ __device__ __forceinline__ void each_terms(float (&acc)[kBRows][NCH], float (&do
         each_terms<R0, U + 1, NCH>(acc, dot, f, g, pv, tail_ok);
     }
 }
-template <int R0, int NCH, bool VEC>
+template <int R0, int NCH>
 __device__ __forceinline__ void row_terms_each(float (&acc)[kBRows][NCH], float (&dot)[kBRows],
                                                const Row<NCH> (&f)[kBRows], Rsrc G, uint32_t g_ch,
                                                int C, int cell, float pv, bool tail_ok) {
     if constexpr (R0 < kBRows) {
         Row<NCH> g[kBEach];
-        each_loads<R0, 0, NCH, VEC>(g, G, g_ch, C, cell);
+        each_loads<R0, 0, NCH>(g, G, g_ch, C, cell);
         each_terms<R0, 0, NCH>(acc, dot, f, g, pv, tail_ok);
-        row_terms_each<R0 + kBEach, NCH, VEC>(acc, dot, f, G, g_ch, C, cell, pv, tail_ok);
+        row_terms_each<R0 + kBEach, NCH>(acc, dot, f, G, g_ch, C, cell, pv, tail_ok);
     }
 }
 
 template <int NCH>
 constexpr int bwd_stride() { return kBRows * NCH * 16 + 16; }   // one lane group's dF sums in LDS
 
-// (held to three waves per SIMD at five values a lane, which 169 registers miss)
-template <int DT, int NCH, bool VEC>
+// (five values a lane: held to the 168 registers of three waves per SIMD)
+template <int DT, int NCH>
 __global__ __launch_bounds__(kBBlock) __attribute__((amdgpu_waves_per_eu(NCH == 5 ? 3 : 1)))
 void k_backward(BwdArgs a) {
     __shared__ float s_df[(kBWaves - 1) * kBCols * bwd_stride<NCH>()];
@@ -262,7 +262,7 @@ void k_backward(BwdArgs a) {
     const uint32_t f_col = in_w ? (uint32_t(n * a.HW + h0 * a.W + w) * uint32_t(a.C) + uint32_t(a.c0)) * ES : kOff;
 #pragma unroll
     for (int r = 0; r < kBRows; ++r) {
-        load_row<DT, NCH, VEC>(f[r], F, h0 + r < a.H ? f_col + uint32_t(r) * f_row : kOff);
+        load_row<DT, NCH, false>(f[r], F, h0 + r < a.H ? f_col + uint32_t(r) * f_row : kOff);
         // the last value of a tail lane lies past the slice: it must not
         // enter the dot products
         if (!tail_ok) f[r].v[NCH - 1] = 0.f;
@@ -293,7 +293,7 @@ void k_backward(BwdArgs a) {
             const uint32_t p = pt0 + uint32_t(dc + i) * uint32_t(a.HW);
             st.cell = ok && row_ok ? int(__builtin_amdgcn_raw_buffer_load_b32(cop, int(p * 4u), 0, 0)) : -1;
             st.pv = Elem<DT>::load(P, ok && row_ok ? p * ES : kOff);
-            load_row<BEVPOOL_F32, NCH, VEC>(st.g, G, st.cc >= 0 ? uint32_t(st.cc) * gC + g_ch : kOff);
+            load_row<BEVPOOL_F32, NCH, false>(st.g, G, st.cc >= 0 ? uint32_t(st.cc) * gC + g_ch : kOff);
         };
         BStage<NCH> st[kBStages];
 #pragma unroll
@@ -313,7 +313,7 @@ void k_backward(BwdArgs a) {
                 if (st[u].cc >= 0) {
                     RowTerms<0, NCH>::run(acc, dot, f, st[u].g, pv);
                 } else if (st[u].cc == -2) {
-                    row_terms_each<0, NCH, VEC>(acc, dot, f, G, g_ch, a.C, st[u].cell, pv, tail_ok);
+                    row_terms_each<0, NCH>(acc, dot, f, G, g_ch, a.C, st[u].cell, pv, tail_ok);
                 } else {
 #pragma unroll
                     for (int r = 0; r < kBRows; ++r) dot[r] = 0.f;
@@ -367,7 +367,7 @@ void k_backward(BwdArgs a) {
     float zero = 0.f;                          // NaN once a sum is not finite
 #pragma unroll
     for (int r = 0; r < kBRows; ++r) {
-        store_row<NCH, VEC>(dF, h0 + r < a.H ? df_col + uint32_t(r) * df_row : kOff, acc[r], tail_ok);
+        store_row<NCH, false>(dF, h0 + r < a.H ? df_col + uint32_t(r) * df_row : kOff, acc[r], tail_ok);
 #pragma unroll
         for (int k = 0; k < NCH; ++k) zero = __builtin_fmaf(acc[r][k], 0.f, zero);
     }
@@ -383,10 +383,10 @@ void k_backward(BwdArgs a) {
         const uint32_t mine = uint32_t(bad >> (r * NCH)) & ((1u << NCH) - 1u);
         if (__ballot(mine != 0u) == 0) continue;
         // (a group without one runs along)
-        const Row<NCH> x = kept_row<DT, NCH, VEC>(P, G, a.cop, n, a.D, a.H, a.W, a.C, h0 + r, w, in_w && h0 + r < a.H, a.c0, j);
+        const Row<NCH> x = kept_row<DT, NCH>(P, G, a.cop, n, a.D, a.H, a.W, a.C, h0 + r, w, in_w && h0 + r < a.H, a.c0, j);
 #pragma unroll
         for (int k = 0; k < NCH; ++k)
-            store_f32(dF, mine >> k & 1u ? df_col + uint32_t(r) * df_row + uint32_t(VEC && k < 4 ? 4 * j + k : j + 16 * k) * 4u : kOff, x.v[k]);
+            store_f32(dF, mine >> k & 1u ? df_col + uint32_t(r) * df_row + uint32_t(j + 16 * k) * 4u : kOff, x.v[k]);
     }
 }
 
@@ -760,7 +760,7 @@ void k_backward_mma(MmaArgs a) {
             }
             if (__ballot(bad != 0) != 0) {
                 // (a group without one runs along: its rows are not taken)
-                const Row<T> x = kept_row<DT, T, false>(P, G, a.cop, n, a.D, a.H, a.W, a.C, h, w, in, a.c0, j);
+                const Row<T> x = kept_row<DT, T>(P, G, a.cop, n, a.D, a.H, a.W, a.C, h, w, in, a.c0, j);
 #pragma unroll
                 for (int t = 0; t < T; ++t) v[t] = bad >> t & 1 ? x.v[t] : v[t];
             }
@@ -820,16 +820,14 @@ bool four_columns(int tiles, int64_t bins, bool level, int piece) {
 }
 
 template <int DT>
-void launch_bwd(const BwdArgs &a, dim3 grid, int nch, bool vec, hipStream_t s) {
+void launch_bwd(const BwdArgs &a, dim3 grid, int nch, hipStream_t s) {
+    const dim3 block(kBBlock);
     switch (nch) {
-        case 1: hipLaunchKernelGGL((k_backward<DT, 1, false>), grid, dim3(kBBlock), 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_backward<DT, 2, false>), grid, dim3(kBBlock), 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_backward<DT, 3, false>), grid, dim3(kBBlock), 0, s, a); break;
-        case 4: hipLaunchKernelGGL((k_backward<DT, 4, false>), grid, dim3(kBBlock), 0, s, a); break;
-        default:
-            if (vec) hipLaunchKernelGGL((k_backward<DT, 5, true>), grid, dim3(kBBlock), 0, s, a);
-            else hipLaunchKernelGGL((k_backward<DT, 5, false>), grid, dim3(kBBlock), 0, s, a);
-            break;
+        case 1: hipLaunchKernelGGL((k_backward<DT, 1>), grid, block, 0, s, a); break;
+        case 2: hipLaunchKernelGGL((k_backward<DT, 2>), grid, block, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((k_backward<DT, 3>), grid, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL((k_backward<DT, 4>), grid, block, 0, s, a); break;
+        default: hipLaunchKernelGGL((k_backward<DT, 5>), grid, block, 0, s, a); break;
     }
 }
 
@@ -916,11 +914,6 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
     const int n_slices = (channels + kBwdSliceChannels - 1) / kBwdSliceChannels;
     const int slice_c = (channels + n_slices - 1) / n_slices;
     const int nch = (slice_c + 15) / 16;
-    const bool vec = nch == 5 && channels % 4 == 0 && slice_c % 4 == 0 &&
-                     reinterpret_cast<uintptr_t>(F) % (4 * esize) == 0 &&
-                     reinterpret_cast<uintptr_t>(G) % 16 == 0 &&
-                     (dF == nullptr || reinterpret_cast<uintptr_t>(dF) % 16 == 0);
-
     BwdArgs a;
     a.P = static_cast<const char *>(P);
     a.F = static_cast<const char *>(F);
@@ -953,9 +946,9 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
         a.cn = std::min(slice_c, channels - a.c0);
         a.accumulate_dp = s > 0;
         switch (dtype) {
-            case BEVPOOL_F32: launch_bwd<BEVPOOL_F32>(a, grid, nch, vec, stream); break;
-            case BEVPOOL_BF16: launch_bwd<BEVPOOL_BF16>(a, grid, nch, vec, stream); break;
-            default: launch_bwd<BEVPOOL_F16>(a, grid, nch, vec, stream); break;
+            case BEVPOOL_F32: launch_bwd<BEVPOOL_F32>(a, grid, nch, stream); break;
+            case BEVPOOL_BF16: launch_bwd<BEVPOOL_BF16>(a, grid, nch, stream); break;
+            default: launch_bwd<BEVPOOL_F16>(a, grid, nch, stream); break;
         }
         BEVPOOL_HIP(hipGetLastError());
     }
