@@ -29,20 +29,20 @@
 // cameras x 118 bins x 32 x 88, C = 80, level, fp32, in cache. There the loads in
 // flight count: two columns at three waves per SIMD take 22.8 us, four at two
 // 24.4; cameras tilted by 1 degree 31 and 36 us, by 5 degrees 49 and 61 us (the
-// kernel below: 57 us in the last two, 84 us in 16 bits). 128 channels in one
+// kernel below: 56 us in the last two). 128 channels in one
 // launch read P once (236 bins x 64 x 176: 322 us in two launches of 80 and 48
 // channels, 165 us in one), with a dP product in two sums: one of 128 products
 // rounds worse, 2.0e-7 against 1.5e-7 from exact. Tried and no faster: 8 waves
 // per workgroup; three waves per SIMD with four columns, by spilling; the next
 // two columns' rows in flight; two columns' products interleaved.
 //
-// k_backward (other rows): pixel-stationary work on the vector ALUs. A
-// workgroup owns kBCols pixel columns x kBRows rows of one camera, and its
-// kBWaves waves take consecutive parts of the depth bins. A group of 16
-// lanes owns one column; lane j holds channels j, j + 16, ... of the slice of
-// the kBRows feature rows, read once, and the kBRows rows' dF sums. For each
-// depth bin the group reads one gradient row when the
-// combo (camera, depth bin, column) is clean, or one per kept row otherwise.
+// k_backward (other rows, and where by_rows says so): pixel-stationary work on
+// the vector ALUs. A workgroup owns kBCols pixel columns x kBRows rows of one
+// camera, and its kBWaves waves take consecutive parts of the depth bins. A
+// group of 16 lanes owns one column; lane j holds channels j, j + 16, ... of the
+// slice of the kBRows feature rows, read once, and the kBRows rows' dF sums. For
+// each depth bin the group reads one gradient row when the combo (camera, depth
+// bin, column) is clean, or one per kept row otherwise.
 // dF gets P x G; dP gets the dot product F . G, reduced across the 16 lanes
 // by a transpose-reduce (8 shuffles for the 8 rows' sums). A wave parks the
 // dP values of a chunk of depth bins in LDS and writes them after the chunk
@@ -819,6 +819,28 @@ bool four_columns(int tiles, int64_t bins, bool level, int piece) {
     return bins >= (level ? 90000 : 150000);
 }
 
+// Whether the per-row kernel is the faster one although the matrix cores could
+// take the call, for `slots` slots in `bins` depth bins of the lists. Its time
+// hardly grows with the slots, but with the slices: two above 80 channels, where
+// the matrix cores take one up to 128. Times in us, rows against matrix cores, 32 x
+// 88 x 118 bins, six cameras, one frame, fp32 unless said:
+//   80 channels: tilted by 6 degrees (3.8 slots to a bin) 56 / 53, 8 (4.4) 56 / 64,
+//   12 (5.3) 54 / 71, every point in a cell of its own (16) 121 / 151; four frames
+//   173 / 139, 173 / 162, 177 / 192, 436 / 487; bf16 54 / 53, 54 / 64, 54 / 71, 122 / 154.
+//   64: 50 / 46, 50 / 56, 50 / 61, 87 / 128. 128: 101 / 82, 101 / 97, 101 / 105, 178 / 242.
+//   96 (rows of two slices of 48): 93 / 73 at 4.4, 92 / 82, 104 / 96 at 8, 178 / 174.
+//   32: 45 / 44 at 5.3, 47 / 48 at 8, 49 / 88 at 16; 16: 44 / 36, 46 / 38, 47 / 68.
+//   One camera (44 lists), 80: 34 / 41 at 5.3, 46 / 40 at 8, 47 / 73 at 16; 128: 76 /
+//   53, 81 / 52, 86 / 96.
+// Level, 87 columns (no piece to move), 16 channels: one frame (31 thousand bins)
+// 22.8 / 22.9, two 31 / 37, eight 98 / 111; 32 channels, two 43 / 39.
+bool by_rows(int64_t slots, int64_t bins, int64_t lists, int batch, int channels, int piece) {
+    if (slots == bins) return piece == 1 && channels <= 16 && bins * batch >= 50000;
+    if (channels > 80 && channels <= 96) return false;
+    const bool few = channels <= 32 || lists * batch < 256;
+    return slots > (few ? 8 : 5) * bins;
+}
+
 template <int DT>
 void launch_bwd(const BwdArgs &a, dim3 grid, int nch, hipStream_t s) {
     const dim3 block(kBBlock);
@@ -856,17 +878,27 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
     if (batch > 65535)
         return bevpool_fail(BEVPOOL_ERR_INVALID_ARG, "batch=%d exceeds 65535 frames per call", batch);
 
+    // v columns of P and of dP move as one piece
+    auto pieces = [&](int v) {
+        return g.feat_w % v == 0 && reinterpret_cast<uintptr_t>(P) % (v * esize) == 0 &&
+               reinterpret_cast<uintptr_t>(dP) % (4 * v) == 0;
+    };
+    const int piece = pieces(4) ? 4 : pieces(2) ? 2 : 1;
+    const int32_t quads_w = (g.feat_w + kBwdCols - 1) / kBwdCols, blocks_h = (g.feat_h + kBwdRows - 1) / kBwdRows;
+    const int64_t lists = int64_t(g.n_cams) * quads_w * blocks_h, bins = lists * g.n_depth;
+
     // Matrix-core kernel where feature and gradient rows move as 4-element
     // quads: channels % 4 == 0 and aligned rows. Otherwise the per-row kernel.
     const bool quads = channels % 4 == 0 && reinterpret_cast<uintptr_t>(F) % (4 * esize) == 0 &&
                        reinterpret_cast<uintptr_t>(G) % 16 == 0;
-    if (quads) {
+    if (quads && !by_rows(plan->n_bwd_slots, bins, lists, batch, channels, piece)) {
         MmaArgs m;
         m.P = static_cast<const char *>(P);
         m.F = static_cast<const char *>(F);
         m.G = G;
         m.dP = dP;
         m.dF = dF;
+        m.cop = plan->cell_of_point;
         m.offs = plan->bwd_offs;
         m.bins = plan->bwd_bins;
         m.cells = plan->bwd_cells;
@@ -880,21 +912,13 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
         m.g_bytes = uint32_t(g_bytes);
         m.dp_bytes = dP ? uint32_t(dp_bytes) : 0u;
         m.df_bytes = dF ? uint32_t(df_bytes) : 0u;
-        m.quads_w = (g.feat_w + kBwdCols - 1) / kBwdCols;
-        m.blocks_h = (g.feat_h + kMRows - 1) / kMRows;
-        m.cop = plan->cell_of_point;
+        m.quads_w = quads_w;
+        m.blocks_h = blocks_h;
         m.want_dp = dP != nullptr;
         m.want_df = dF != nullptr;
-        // v columns of P and of dP move as one piece
-        auto pieces = [&](int v) {
-            return g.feat_w % v == 0 && reinterpret_cast<uintptr_t>(P) % (v * esize) == 0 &&
-                   reinterpret_cast<uintptr_t>(dP) % (4 * v) == 0;
-        };
-        const int piece = pieces(4) ? 4 : pieces(2) ? 2 : 1;
-        const int64_t lists = int64_t(g.n_cams) * m.quads_w * m.blocks_h, bins = lists * g.n_depth;
         // equal slices of at most kMSlice channels, whole 16-channel tiles
-        const int n_slices = (channels + kMSlice - 1) / kMSlice;
-        const int slice = ((channels + n_slices - 1) / n_slices + 15) / 16 * 16;
+        const int n = (channels + kMSlice - 1) / kMSlice;
+        const int slice = ((channels + n - 1) / n + 15) / 16 * 16;
         for (int c0 = 0; c0 < channels; c0 += slice) {
             m.c0 = c0;
             m.cn = std::min(slice, channels - c0);
@@ -914,6 +938,7 @@ int bevpool_launch_backward(const float *G, const void *P, const void *F,
     const int n_slices = (channels + kBwdSliceChannels - 1) / kBwdSliceChannels;
     const int slice_c = (channels + n_slices - 1) / n_slices;
     const int nch = (slice_c + 15) / 16;
+
     BwdArgs a;
     a.P = static_cast<const char *>(P);
     a.F = static_cast<const char *>(F);

@@ -314,6 +314,43 @@ def test_backward_four_columns(torch_cuda, pkg, oracle_lib, H, W, D, C, tilt, dt
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 43), dtype=dtype)
 
 
+def _imported_check(torch, pkg, oracle_lib, w, cells, G, dtype):
+    """_check's bounds for a plan from a stored cell map."""
+    rig, C = w.rig, w.channels
+    plan = pkg.Plan.from_cells(cells, rig)
+    gd, gf = plan.backward(torch.from_numpy(G).cuda(), _dev(torch, w.P, dtype), _dev(torch, w.F, dtype))
+    torch.cuda.synchronize()
+    refP, refF = oracle_lib.backward(rig, cells, _host_values(torch, w.P, dtype), _host_values(torch, w.F, dtype), G)
+    got = gd.cpu().numpy().reshape(w.batch, -1).astype(np.float64)
+    assert (np.abs(got - refP.reshape(got.shape)) <= 1e-4 * np.sqrt(C)).all()
+    assert (got[:, cells < 0] == 0).all()
+    k = (cells >= 0).reshape(rig.n_cams, rig.n_depth, -1).sum(axis=1).reshape(-1)
+    got = gf.cpu().numpy().reshape(w.batch, rig.n_pixels, C).astype(np.float64)
+    assert (np.abs(got - refF.reshape(got.shape)) <= 1e-4 * np.sqrt(np.maximum(k, 1))[None, :, None]).all()
+    plan.close()
+
+
+@pytest.mark.parametrize("H,W,D,C,rows,dtype,batch", [
+    (33, 8, 40, 80, 1, "f32", 2),      # 16 slots to a bin: the per-row kernel
+    (17, 10, 33, 148, 1, "bf16", 3),   # two slices of it, the second adds to dP
+    (13, 9, 20, 16, 1, "f16", 2),      # 16 channels; 13 rows in 13 cells
+    (33, 8, 40, 88, 1, "f32", 2),      # 88 channels: the matrix cores at any number of slots
+    (33, 8, 40, 64, 2, "f32", 2),      # 8 slots to a bin: few workgroups stay on the matrix cores
+    (33, 8, 40, 64, 2, "f32", 22),     # 264 lists do not
+    (33, 7, 1100, 8, 40, "f32", 4),    # one slot to a bin, odd W, few channels: the per-row kernel
+])
+def test_backward_by_slots(torch_cuda, pkg, oracle_lib, H, W, D, C, rows, dtype, batch):
+    """Both sides of the rule that takes calls of many slots to a bin (cells that
+    change every `rows` rows) to the per-row kernel, and odd level maps of few
+    channels."""
+    _say(f"[backward by slots] H={H} W={W} D={D} C={C} rows={rows} {dtype} batch={batch}")
+    w = _edge_workload(H, W, D, C, 0.0, dtype, seed=46, batch=batch)
+    rng = np.random.default_rng(47)
+    cells = rng.integers(-1, 1600, (2, D, -(-H // rows), W)).repeat(rows, axis=2)[:, :, :H]
+    _imported_check(torch_cuda, pkg, oracle_lib, w, np.ascontiguousarray(cells, dtype=np.int32).reshape(-1),
+                    _grad(w, 48), dtype)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("offset", [1, 2])
 def test_backward_unaligned_probabilities(torch_cuda, pkg, dtype, offset):
