@@ -835,6 +835,7 @@ bool four_columns(int tiles, int64_t bins, bool level, int piece) {
 // Level, 87 columns (no piece to move), 16 channels: one frame (31 thousand bins)
 // 22.8 / 22.9, two 31 / 37, eight 98 / 111; 32 channels, two 43 / 39.
 bool by_rows(int64_t slots, int64_t bins, int64_t lists, int batch, int channels, int piece) {
+    if (slots == 0) return true;               // a plan without lists
     if (slots == bins) return piece == 1 && channels <= 16 && bins * batch >= 50000;
     if (channels > 80 && channels <= 96) return false;
     const bool few = channels <= 32 || lists * batch < 256;

@@ -104,7 +104,7 @@ struct bevpool_plan_s {
     int4 *bwd_cells;         // [slots]: the columns' cells, -1 for none
     int4 *bwd_masks;         // [slots]: 16-bit row masks by column: x, y kept rows; z, w rows whose dP it writes
     int32_t *bwd_bins;       // [slots]: depth bin
-    int32_t n_bwd_slots;
+    int32_t n_bwd_slots;     // 0: no lists
     int32_t *multi_begin;    // [n_multi + 1]: first partial slot of each multi-combo cell
     int32_t *multi_cell;     // [n_multi]
     int32_t *multi_rows;     // [n_multi][kCombineInline]: borrowed rows of the first slots, or -1

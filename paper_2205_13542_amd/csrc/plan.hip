@@ -1095,6 +1095,12 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
     const int32_t quads_w = (W + kBwdCols - 1) / kBwdCols, blocks_h = (H + kBwdRows - 1) / kBwdRows;
     const int32_t n_lists = N * quads_w * blocks_h;     // backward lists, n_bwd (list, depth bin) pairs:
     const int32_t n_bwd = n_lists * D;                  // at most one for each point
+    // No lists (the backward then takes the per-row kernel) where a launch of one
+    // workgroup for each list, or two, would not fit a grid's 2^32 threads, or
+    // where the slots might not fit int32: a bin of the most pieces, one a row, with
+    // all but one of them as empty slots before it.
+    const bool lists = n_lists < (1 << 23) &&
+                       int64_t(n_bwd) * (2 * std::min(H, kBwdRows) - 1) <= int64_t(INT32_MAX);
     plan->n_points = np64;
     plan->n_cells = n_cells;
     plan->nz = nz;
@@ -1265,7 +1271,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         ca.seg_range = seg_range;
         ca.counters = small;
         // the backward lists' slots are counted here; their number comes back
-        // with the counts of the first classification
+        // with the counts of the first classification (0 without lists)
         BwdListArgs bl;
         bl.cell_of_point = plan->cell_of_point;
         bl.N = N;
@@ -1281,9 +1287,11 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         bl.n_lists = n_lists;
         if ((rc2 = arena.take(&bl.counts, size_t(n_bwd), "backward slots"))) return rc2;
         bl.offs = plan->bwd_offs;
-        hipLaunchKernelGGL(k_bwd_counts, dim3(blocks_for(n_bwd)), dim3(kBlock), 0, stream, bl);
-        hipLaunchKernelGGL(k_bwd_places, dim3(n_lists), dim3(kBlock), 0, stream, bl);
-        device_scan(bl.offs, int64_t(n_lists) + 1, small + 12, scan_sums, stream);
+        if (lists) {
+            hipLaunchKernelGGL(k_bwd_counts, dim3(blocks_for(n_bwd)), dim3(kBlock), 0, stream, bl);
+            hipLaunchKernelGGL(k_bwd_places, dim3(n_lists), dim3(kBlock), 0, stream, bl);
+            device_scan(bl.offs, int64_t(n_lists) + 1, small + 12, scan_sums, stream);
+        }
         // (k_combo_table writes every entry of every plane: no clearing first)
         hipLaunchKernelGGL(k_combo_walk, dim3(reduce_blocks(n_combo)), dim3(kBlock), 0, stream, ca);
         int32_t stats[4], counters[2], n_gen = 0, n_empty = 0, kept = 0, n_part = 0;
@@ -1371,7 +1379,7 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         bl.cells = plan->bwd_cells;
         bl.masks = plan->bwd_masks;
         bl.bins = plan->bwd_bins;
-        hipLaunchKernelGGL(k_bwd_lists, dim3(blocks_for(n_bwd)), dim3(kBlock), 0, stream, bl);
+        if (lists) hipLaunchKernelGGL(k_bwd_lists, dim3(blocks_for(n_bwd)), dim3(kBlock), 0, stream, bl);
         hipLaunchKernelGGL(k_empty_list, dim3(blocks_for(n_cells)), dim3(kBlock), 0, stream, flag_b,
                            n_cells, plan->empty_cells);
 

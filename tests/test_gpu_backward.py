@@ -443,3 +443,43 @@ def test_backward_infinite_gradient(torch_cuda, pkg, C):
     _say(f"[backward infinite] C={C}: finite {finite:.1f} us, infinite {infinite:.1f} us")
     assert infinite <= 12.0 * finite
     plan.close()
+
+
+@pytest.mark.parametrize("width,backward", [((1 << 25) + 4, True), ((1 << 26) + 4, False)])
+def test_plan_without_backward_lists(torch_cuda, pkg, width, backward):
+    """One row, one bin and so many columns that the backward lists (four columns
+    each) would not fit a grid of two workgroups, or one, for each: the plan has
+    none, and where the per-row kernel's grid fits, forward and backward work.
+    One point in 64 is kept; each pixel has one point, so gradients are exact."""
+    torch = torch_cuda
+    _say(f"[lists] {width} columns")
+    base = wl.ring_rig()
+    rig = dataclasses.replace(base, n_cams=1, feat_h=1, feat_w=width, n_depth=1, nx=1024, ny=1024,
+                              intrinsics=base.intrinsics[:1].copy(), extrinsics=base.extrinsics[:1].copy())
+    C = 4 if backward else 1
+    rng = np.random.default_rng(70)
+    at = np.sort(rng.choice(width // 64, width // 128, replace=False).astype(np.int64) * 64 + 63)
+    cells = np.full(width, -1, np.int32)
+    cells[at] = rng.integers(0, 1 << 20, at.size)
+    plan = pkg.Plan.from_cells(cells, rig)
+    assert plan.info.n_kept == at.size
+    if not backward:
+        plan.close()
+        return
+    at, to = torch.from_numpy(at).cuda(), torch.from_numpy(cells[at].astype(np.int64)).cuda()
+    g = torch.Generator(device="cuda").manual_seed(71)
+    P = torch.rand((1, 1, 1, 1, width), generator=g, device="cuda")
+    F = torch.randn((1, 1, 1, width, C), generator=g, device="cuda")
+    out = plan.forward(P, F).reshape(-1, C)
+    p, f = P.reshape(-1)[at].double(), F.reshape(-1, C)[at].double()
+    ref = torch.zeros((1 << 20, C), dtype=torch.float64, device="cuda").index_add_(0, to, p[:, None] * f)
+    assert float((out - ref).abs().max()) <= 1e-4
+    if backward:
+        G = torch.randn((1, 1024, 1024, C), generator=g, device="cuda")
+        gd, gf = plan.backward(G, P, F)
+        rows = G.reshape(-1, C)[to]
+        assert torch.equal(gf.reshape(-1, C)[at], P.reshape(-1)[at][:, None] * rows)
+        ref = (f * rows.double()).sum(1)
+        assert float((gd.reshape(-1)[at] - ref).abs().max()) <= 1e-4 * C ** 0.5
+        assert int((gd != 0).sum()) <= at.numel() and int((gf != 0).sum()) <= at.numel() * C
+    plan.close()
