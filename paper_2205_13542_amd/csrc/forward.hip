@@ -333,16 +333,18 @@ __device__ void column_item(const FwdArgs &a, const Frame &fr, int item, int c0,
 #pragma unroll
     for (int q = 0; q < kWarmArrays; ++q) wfirst[q] = 0;
     if (blockIdx.y == 0 && blockIdx.z == 0) {
-        const int stride = a.n_items * kFwdBlock;
-        const int i0 = item * kFwdBlock + int(threadIdx.x);
+        // (unsigned: with 2^23 items and more, the second word of a thread lies
+        // past int, and a negative index would pass the comparison)
+        const uint32_t stride = uint32_t(a.n_items) * kFwdBlock;
+        const uint32_t i0 = uint32_t(item) * kFwdBlock + threadIdx.x;
 #pragma unroll
         for (int q = 0; q < kWarmArrays; ++q) {
             const Rsrc wr = make_rsrc(a.warm[q], uint32_t(a.warm_n[q]) * 4u);
-            wfirst[q] = int(__builtin_amdgcn_raw_buffer_load_b32(wr, i0 < a.warm_n[q] ? i0 * 4 : int(kOff), 0, 0));
+            wfirst[q] = int(__builtin_amdgcn_raw_buffer_load_b32(wr, int(i0 < uint32_t(a.warm_n[q]) ? i0 * 4u : kOff), 0, 0));
         }
 #pragma unroll
         for (int q = 0; q < kWarmArrays; ++q)
-            for (int i = i0 + stride; i < a.warm_n[q]; i += stride) warm ^= a.warm[q][i];
+            for (uint32_t i = i0 + stride; i < uint32_t(a.warm_n[q]); i += stride) warm ^= a.warm[q][i];
     }
 
     // Row segments (SEG): a combo whose kept rows fall into several cells
