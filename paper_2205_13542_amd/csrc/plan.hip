@@ -1163,19 +1163,23 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         {
             // upper bounds of every temporary taken below: the partial slots
             // (n_part) are at most the combos, the kept points at most the
-            // points, the generic cells at most the cells
+            // points, the generic cells at most the cells. The runtime keeps
+            // about 64 MB of freed memory to hand out again and unmaps what is
+            // beyond (270 us a piece), which a plan closed before the next one is
+            // built should stay below: 53 MB of block and plan for 2 M points.
             const size_t i4 = sizeof(int32_t);
             const size_t sort_b = Arena::piece(size_t(sort_cap) * i4);
             const size_t cells1_b = Arena::piece((size_t(n_cells) + 1) * i4);
             const size_t combo1_b = Arena::piece((size_t(n_seg) + 1) * i4);
-            arena.cap = Arena::piece(size_t(g.n_cams) * 16 * sizeof(double)) + 4 * sort_b +
+            arena.cap = Arena::piece(size_t(g.n_cams) * 16 * sizeof(double)) +
+                        Arena::piece((size_t(sort_cap) + 1) * i4) + 2 * sort_b +   // keys_a, keys_b, vals_b
+                        Arena::piece(size_t(std::max<int64_t>(n_seg, n_cells)) * i4) +   // vals_a
                         Arena::piece(size_t(sort_tiles_cap) * kRadixBins * i4) +
                         Arena::piece(size_t(kShards) * kCounters * i4) + Arena::piece(size_t(kScanSums) * i4) +
                         5 * cells1_b +                 // flag_a, flag_b, cell_generic, cell_ncombo, run_begin
                         Arena::piece(size_t(n_cells) * i4) +          // pos_of_cell
                         2 * combo1_b +                 // combo_flag, head_scan
                         2 * Arena::piece(size_t(n_seg) * i4) +        // seg_cell, seg_range
-                        Arena::piece((size_t(np) + 1) * i4) +         // run_scan
                         Arena::piece(size_t(n_bwd) * i4);             // bwd_counts
             const size_t need = arena.cap;
             arena.base = bevpool_workspace_out(plan->device, &arena.cap);
@@ -1189,9 +1193,10 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
         if (!host_cells && !cal_in_args &&
             (rc2 = arena.take(&d_calib, size_t(g.n_cams) * 16, "calibration")))
             return rc2;
-        if ((rc2 = arena.take(&keys_a, size_t(sort_cap), "sort keys"))) return rc2;
+        // (vals_a serves the sorts of the slots and of the gathered cells only)
+        if ((rc2 = arena.take(&keys_a, size_t(sort_cap) + 1, "sort keys"))) return rc2;
         if ((rc2 = arena.take(&keys_b, size_t(sort_cap), "sort keys"))) return rc2;
-        if ((rc2 = arena.take(&vals_a, size_t(sort_cap), "sort values"))) return rc2;
+        if ((rc2 = arena.take(&vals_a, size_t(std::max<int64_t>(n_seg, n_cells)), "sort values"))) return rc2;
         if ((rc2 = arena.take(&vals_b, size_t(sort_cap), "sort values"))) return rc2;
         if ((rc2 = arena.take(&hist, size_t(sort_tiles_cap) * kRadixBins, "radix histogram"))) return rc2;
         // kShards shards of counters: [0..1] cell stats, [2] planes in use, [3]
@@ -1434,8 +1439,9 @@ int bevpool_build_plan(const double *intrinsics, const double *extrinsics,
                               scan_sums, stream)))
             return rc2;
 
-        // runs of the generic cells, in list order
-        if ((rc2 = arena.take(&run_scan, size_t(kept) + 1, "run flags"))) return rc2;
+        // runs of the generic cells, in list order (their flags in the keys'
+        // place: the sort has left the cells in vals_a or vals_b)
+        run_scan = reinterpret_cast<int32_t *>(keys_a);
         if ((rc2 = arena.take(&run_begin, size_t(n_gen) + 1, "run offsets"))) return rc2;
         if ((rc2 = arena.take(&pos_of_cell, size_t(n_cells), "cell positions"))) return rc2;
         const FastDiv div_hw = make_fastdiv(uint32_t(HW)), div_d = make_fastdiv(uint32_t(D));
