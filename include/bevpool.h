@@ -20,7 +20,11 @@
  *  - Pointers marked "host" are ordinary CPU memory. Pointers marked "device"
  *    are HIP device memory on the current device.
  *  - The caller owns every input and output buffer. The library owns the
- *    plan and its device buffers until bevpool_plan_destroy.
+ *    plan and its device buffers until bevpool_plan_destroy. Beside them, while
+ *    a device has plans, it keeps one block of its plan builds' temporaries
+ *    there for the next build, of at most 512 MiB (32 MB for 2 M points; larger
+ *    blocks are freed after the build). Destroying the device's last plan frees
+ *    it, and so does an allocation of the library that fails.
  *  - hip_stream is a hipStream_t passed as void*; NULL is the null stream.
  */
 #ifndef BEVPOOL_H
@@ -107,7 +111,11 @@ typedef struct bevpool_plan_s bevpool_plan_t;
  *    sorted_point[cell_start[c] .. cell_start[c+1]);
  *  - a work partition used by bevpool_forward.
  *
- * Allocates device memory and synchronises hip_stream before returning.
+ * Allocates device memory and synchronises hip_stream before returning. Plans
+ * may be built on several threads and streams at once. Where a plan replaces
+ * another, building the new one before destroying the old one is the faster
+ * order: the kept block of temporaries then passes from build to build (2 M
+ * points, cameras tilted by 5 degrees: 0.67 against 0.96 ms).
  * The calibration arrays may be freed as soon as the call returns.
  * Errors: INVALID_ARG (null pointer, a size < 1, a non-finite value, a zero
  * focal length, a non-positive step or cell side), OVERFLOW (N*D*H*W or
@@ -230,6 +238,9 @@ BEVPOOL_API int bevpool_forward_timed(const void *depth_prob, const void *cam_fe
  *              skip (not both NULL).
  * Sums are accumulated in fp32 in an order fixed by the plan, so repeated
  * calls give bitwise equal results; no atomics, no allocation, no scratch.
+ * An infinity or a NaN in a cell's row of grad_out reaches grad_depth of the
+ * cell's points and grad_feat of the pixels with a point in the cell, and no
+ * others.
  * Asynchronous on hip_stream. Buffers must not overlap. A plan may be used
  * by several backward and forward calls at once on different streams.
  * Errors: INVALID_ARG (null pointer, a bad plan handle, both outputs NULL,
@@ -341,8 +352,9 @@ BEVPOOL_API int bevpool_associate_noalloc(const double *intrinsics, const double
                               const bevpool_geometry *geom, int32_t *cell_of_point,
                               int32_t *sorted_point, int32_t *cell_start, void *hip_stream);
 
-/* Free a plan and its device memory. NULL-safe. The plan must not be in use
- * by work still queued on a stream. */
+/* Free a plan and its device memory, with the device's last plan also the kept
+ * block of build temporaries. NULL-safe. The plan must not be in use by work
+ * still queued on a stream. */
 BEVPOOL_API void bevpool_plan_destroy(bevpool_plan_t *plan);
 
 /* Message for the last nonzero return on the calling thread ("" if none). */

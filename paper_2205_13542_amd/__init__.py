@@ -104,7 +104,10 @@ class Plan:
 
     ``Plan(intrinsics, extrinsics, geometry)``: intrinsics [N][4] and
     extrinsics [N][12] float64 host arrays; geometry has the
-    bevpool_geometry fields (e.g. a rig object or a dict).
+    bevpool_geometry fields (e.g. a rig object or a dict). While a device has
+    plans the library keeps a block of build temporaries there (at most 512 MiB,
+    outside torch's allocator); the last plan's ``close`` frees it, so a plan
+    that replaces another is best built before the other is closed.
     """
 
     def __init__(self, intrinsics, extrinsics, geometry, stream=None, nz: int = 1):
