@@ -273,6 +273,32 @@ BWD_METRIC = ("BEV-pool backward ms + HBM GB/s (gradients of P and F), 6cam×118
               "→360×360 BEV, 1 GPU")
 
 
+def backward_list_bytes(rig, cells):
+    """Bytes of a plan's backward lists for the cell map ``cells``: one list for
+    each camera, 4 columns and 16 rows, 36 bytes for each of its slots and 4 for
+    its place. A depth bin has as many slots as the most pieces that its rows form
+    in one of the columns (a piece ends where a kept row's cell is another one),
+    and lies within 16 slots: empty slots before it fill the 16."""
+    import numpy as np
+    N, D, H, W = rig.n_cams, rig.n_depth, rig.feat_h, rig.feat_w
+    hb, wb = -(-H // 16), -(-W // 4)
+    x = np.full((N, D, hb * 16, wb * 4), -1, np.int32)
+    x[:, :, :H, :W] = np.asarray(cells).reshape(N, D, H, W)
+    x = x.reshape(N, D, hb, 16, wb * 4)
+    last = np.full((N, D, hb, wb * 4), -1, np.int32)
+    pieces = np.zeros(last.shape, np.int64)
+    for r in range(16):
+        c = x[:, :, :, r]
+        pieces += (c >= 0) & (c != last)
+        last = np.where(c >= 0, c, last)
+    most = np.maximum(1, pieces.reshape(N, D, hb, wb, 4).max(axis=-1))
+    at = np.zeros((N, hb, wb), np.int64)
+    for d in range(D):
+        n = most[:, d]
+        at = np.where(at % 16 + n > 16, (at // 16 + 1) * 16, at) + n
+    return int(36 * at.sum() + 4 * (N * hb * wb + 1))
+
+
 def backward_bench(args):
     """bevpool_backward on the workload: P, F and a standard-normal gradient
     of the BEV map resident in HBM; each timed call after a cache-evicting
@@ -333,9 +359,9 @@ def backward_bench(args):
                         "median": round(float(np.median(ms)) * 1e3, 2),
                         "min": round(float(ms.min()) * 1e3, 2)},
         "algorithmic_bytes": nbytes,
-        # the combo table by column (8 bytes per combo) and the block flags
-        "plan_bytes_read": 8 * w.rig.n_cams * w.rig.n_depth * w.rig.feat_w
-                           + 4 * w.rig.n_cams * -(-w.rig.feat_w // 8),
+        # the lists of the matrix-core kernel, which takes every workload here:
+        # cells, masks and bin of each slot, and the lists' first slots
+        "plan_bytes_read": backward_list_bytes(w.rig, plan.export()[0]),
         "kernel_sha256_16": kernel_hash([BWD_SOURCE]),
     }
     if not args.no_cpu_baseline:

@@ -73,3 +73,30 @@ def test_traffic_hash_covers_every_forward_source(tmp_path):
         assert bench.kernel_hash(copies) != base, q
         open(q, "wb").write(orig)
     assert bench.kernel_hash(copies) == base
+
+
+def test_backward_list_bytes():
+    """One slot for each depth bin of a level rig; on a random map, the count of
+    a walk over every list, bin and column."""
+    import dataclasses
+    import oracle
+    rig = wl.ring_rig()
+    lists = 6 * 2 * 22
+    assert bench.backward_list_bytes(rig, oracle.cell_map(rig)) == 36 * lists * 118 + 4 * (lists + 1)
+    rig = dataclasses.replace(rig, n_cams=2, n_depth=9, feat_h=21, feat_w=6)
+    cells = np.random.default_rng(0).integers(-1, 3, (2, 9, 21, 6))
+    slots = 0
+    for n in range(2):
+        for h0 in (0, 16):
+            for w0 in (0, 4):
+                at = 0
+                for d in range(9):
+                    most = 1
+                    for w in range(w0, min(w0 + 4, 6)):
+                        column = [c for c in cells[n, d, h0:h0 + 16, w] if c >= 0]
+                        most = max(most, sum(1 for i, c in enumerate(column) if i == 0 or c != column[i - 1]))
+                    if at % 16 + most > 16:
+                        at += 16 - at % 16
+                    at += most
+                slots += at
+    assert bench.backward_list_bytes(rig, cells.reshape(-1)) == 36 * slots + 4 * 9
