@@ -100,8 +100,8 @@ def test_backward_reduced_precision_inputs(torch_cuda, pkg, oracle_lib, dtype):
 
 @pytest.mark.parametrize("channels", [1, 5, 17, 64, 81, 160, 260])
 def test_backward_channel_counts(torch_cuda, pkg, oracle_lib, channels):
-    """Every lane-chunk count, 4-element lanes (160), and channel slices
-    (81, 160, 260: dP adds the slices' dot products)."""
+    """The per-row kernel (1, 5, 17, 81) and the matrix cores (64, 160, 260), and
+    channel slices (81, 160, 260: dP adds the slices' dot products)."""
     _say(f"[backward] nuscenes_tilted C={channels}")
     w = wl.make("nuscenes_tilted", seed=5, channels=channels)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, channels))
@@ -173,11 +173,11 @@ def test_autograd_function_matches_oracle(torch_cuda, pkg, oracle_lib):
     plan.close()
 
 
-# ------------------------------------------------------------ matrix-core path
+# ------------------------------------------------------------ the two kernels
 #
-# Level rigs send every block to the matrix-core kernel when the channel count
-# is a multiple of 4 and the rows are aligned; otherwise, and for blocks with a
-# combo that is not clean, the per-row kernel runs.
+# A call with a channel count that is a multiple of 4 and aligned rows runs on
+# the matrix-core kernel, on every rig whose depth bins do not take many slots
+# each (test_backward_by_slots); all other calls run on the per-row kernel.
 
 from test_gpu_parity import RIGS  # noqa: E402
 
@@ -189,9 +189,9 @@ def _rig_workload(rig, channels, seed, batch=1, dtype="f32"):
 
 @pytest.mark.parametrize("channels", [4, 16, 48, 64, 80, 84, 160, 200, 5, 17, 81])
 def test_backward_level_channel_counts(torch_cuda, pkg, oracle_lib, channels):
-    """Matrix-core launches of 1..5 channel tiles, a ragged last tile (84,
-    200: slices of 80 then 4 or 40), several slices adding into dP (160,
-    200); 5, 17 and 81 channels take the per-row kernel."""
+    """Matrix-core launches of 1..8 channel tiles, ragged last tiles (4, 84:
+    one slice of 6 tiles; 200: slices of 112 and 88), two slices adding into dP
+    (160, 200); 5, 17 and 81 channels take the per-row kernel."""
     _say(f"[backward level] nuscenes C={channels}")
     w = _rig_workload(wl.ring_rig(), channels, seed=channels)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, channels + 1))
@@ -199,19 +199,20 @@ def test_backward_level_channel_counts(torch_cuda, pkg, oracle_lib, channels):
 
 @pytest.mark.parametrize("name", ["odd", "odd_tilted", "anisotropic", "coarse", "coarse_tilted",
                                   "one_cell", "empty", "tiny_identity", "tall"])
-@pytest.mark.parametrize("channels", [8, 20])
+@pytest.mark.parametrize("channels", [8, 20, 7, 63])
 def test_backward_edge_rigs(torch_cuda, pkg, oracle_lib, name, channels):
-    """Odd sizes (27 columns: the last column pair has one column; 13 rows: a
-    partial row block; 37 bins: partial depth steps), an empty grid, one
-    cell, cells fed by many combos, and 16,400 rows (no clean combo)."""
+    """Both kernels (8 and 20 channels: matrix cores; 7 and 63: per-row, slices
+    of one and four values a lane) on odd sizes (27 columns: the last list has
+    three; 13 rows: a partial row block; 37 bins: partial depth steps), an empty
+    grid, one cell, cells fed by many combos, and 16,400 rows (no clean combo)."""
     _say(f"[backward edge] {name} C={channels}")
     w = _rig_workload(RIGS[name](), channels, seed=channels + 3)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, channels + 7))
 
 
 def _one_tilted_camera_rig():
-    """The ring rig with camera 0 pitched 5 degrees: its blocks hold combos
-    that are not clean, the other cameras' blocks are all clean."""
+    """The ring rig with camera 0 pitched 5 degrees: its depth bins have several
+    slots and its combos are not clean, the other cameras' are."""
     base = wl.ring_rig()
     tilted = wl.tilt_rig(base, 5.0, 2.0)
     E = base.extrinsics.copy()
@@ -219,37 +220,42 @@ def _one_tilted_camera_rig():
     return dataclasses.replace(base, extrinsics=E)
 
 
+@pytest.mark.parametrize("channels", [80, 67])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_backward_mixed_blocks(torch_cuda, pkg, oracle_lib, dtype):
-    """One call runs both kernels on disjoint blocks."""
-    _say(f"[backward mixed] one tilted camera {dtype}")
-    w = _rig_workload(_one_tilted_camera_rig(), 80, seed=21, batch=2, dtype=dtype)
+def test_backward_mixed_blocks(torch_cuda, pkg, oracle_lib, dtype, channels):
+    """Lists of one and of several slots to a bin in one call of the matrix-core
+    kernel (80 channels); clean and other combos in one of the per-row kernel."""
+    _say(f"[backward mixed] one tilted camera {dtype} C={channels}")
+    w = _rig_workload(_one_tilted_camera_rig(), channels, seed=21, batch=2, dtype=dtype)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 22), dtype=dtype)
 
 
 def test_backward_highres(torch_cuda, pkg, oracle_lib):
-    """6 x 236 bins x 64 x 176, C = 128 (slices of 80 and 48 channels)."""
+    """6 x 236 bins x 64 x 176, C = 128: 8 channel tiles, four columns."""
     _say("[backward highres] C=128")
     w = wl.make("highres", seed=3)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 23))
 
 
-def test_backward_unaligned_features(torch_cuda, pkg, oracle_lib):
-    """F one element past a 16-byte boundary: the per-row kernel takes every
-    block; the result matches the aligned call within the bounds."""
+@pytest.mark.parametrize("tilt,dtype", [(0.0, "f32"), (5.0, "bf16")])
+def test_backward_unaligned_features(torch_cuda, pkg, oracle_lib, tilt, dtype):
+    """F one element past a 16-byte boundary: the per-row kernel takes the call;
+    the result matches the oracle within the bounds."""
     torch = torch_cuda
-    _say("[backward] unaligned F")
-    w = _rig_workload(wl.ring_rig(), 80, seed=24)
+    _say(f"[backward] unaligned F, tilt={tilt} {dtype}")
+    rig = wl.tilt_rig(wl.ring_rig(), tilt, 0.4 * tilt) if tilt else wl.ring_rig()
+    w = _rig_workload(rig, 80, seed=24, dtype=dtype)
     plan = pkg.Plan.from_rig(w.rig)
-    P = _dev(torch, w.P, "f32")
-    buf = torch.empty(w.F.size + 1, dtype=torch.float32, device="cuda")
-    buf[1:] = torch.from_numpy(w.F.reshape(-1)).cuda()
+    P, F = _dev(torch, w.P, dtype), _dev(torch, w.F, dtype)
+    buf = torch.empty(w.F.size + 1, dtype=F.dtype, device="cuda")
+    buf[1:] = F.reshape(-1)
     F_un = buf[1:].view(w.F.shape)
     G = torch.from_numpy(_grad(w, 25)).cuda()
     gd, gf = plan.backward(G, P, F_un)
     torch.cuda.synchronize()
     cop = oracle_lib.cell_map(w.rig)
-    refP, refF = oracle_lib.backward(w.rig, cop, w.P, w.F, _grad(w, 25))
+    refP, refF = oracle_lib.backward(w.rig, cop, _host_values(torch, w.P, dtype), _host_values(torch, w.F, dtype),
+                                     _grad(w, 25))
     assert (np.abs(gd.cpu().numpy().astype(np.float64) - refP) <= 1e-4 * np.sqrt(80)).all()
     k = (cop >= 0).reshape(w.rig.n_cams, w.rig.n_depth, -1).sum(axis=1).reshape(-1)
     bound = 1e-4 * np.sqrt(np.maximum(k, 1))[None, :, None]
@@ -292,9 +298,16 @@ def _edge_workload(H, W, D, C, tilt, dtype, seed, batch=2):
     (31, 12, 40, 132, 5.0, "f32"),    # two slices, the second adds to dP
     (20, 7, 300, 96, 1.0, "bf16"),    # 6 tiles, odd W, lists of several steps per wave
     (16, 4, 1100, 8, 6.0, "f32"),     # more bins than are placed at a time
+    # the per-row kernel (8 rows x 4 columns, chunks of 32 bins, slices of at most 80 channels):
+    (8, 4, 32, 15, 0.0, "bf16"),      # one whole block and chunk, one value a lane
+    (7, 3, 31, 31, 8.0, "f16"),       # one short of each, two values
+    (9, 5, 33, 45, 3.0, "bf16"),      # one past each, three values
+    (17, 6, 130, 63, 8.0, "f16"),     # a chunk and two bins to a wave, four values
+    (12, 7, 40, 79, 1.0, "bf16"),     # five values, the last of one lane short
+    (20, 9, 70, 162, 5.0, "f16"),     # three slices of 54, the later ones add to dP
 ])
 def test_backward_tile_edges(torch_cuda, pkg, oracle_lib, H, W, D, C, tilt, dtype):
-    """The matrix-core kernel at the edges of its tiles, steps and slices."""
+    """Both kernels at the edges of their tiles, steps, chunks and slices."""
     _say(f"[backward edges] H={H} W={W} D={D} C={C} tilt={tilt} {dtype}")
     w = _edge_workload(H, W, D, C, tilt, dtype, seed=40)
     _check(torch_cuda, pkg, oracle_lib, w, _grad(w, 41), dtype=dtype)
