@@ -139,12 +139,16 @@ constexpr int kOnePlane = 0, kStored = 1, kQueued = 2;
 // order on one counter). Groups start on different bank quarters.
 //
 // The queue leaves a CU four workgroups at 80 channels where registers alone
-// allow six to eight, so it is for calls whose column items are all resident
-// with it and that gather no cells (80 channels, 1-degree rig, one bf16 frame:
-// 54.6 -> 47.3 us with the layout copy). Beyond that the stored form is faster:
-// four frames 105 against 114 us, and the gathered cells beside the items wait
-// for loads at half the waves (2-degree rig, 60 against 80 us; 3-degree rig, 92
-// against 126 us; 128 channels, 1-degree rig, 42 against 58 us).
+// allow six to eight, so it is for calls whose column items its LDS can hold all
+// at once and that gather no cells (80 channels, 1-degree rig, one bf16 frame: 54.6
+// -> 47.3 us with the layout copy). Beyond that the stored form is faster: four
+// frames 105 against 114 us, and the gathered cells beside the items wait for
+// loads at half the waves (2-degree rig, 60 against 80 us; 3-degree rig, 92 against
+// 126 us; 128 channels, 1-degree rig, 42 against 58 us). At fewer channels the LDS
+// holds more workgroups than the registers (19 to a CU at 16 channels), and the
+// queue is the faster form up to there, also where not all items are resident
+// (forward alone, 1-degree rig, fp32, stored against queued: 16 channels, one
+// frame 32 / 26 us, four 66 / 52; 48 channels, one frame 37 / 31).
 constexpr int kQueueChunks = 5;    // 16-channel chunks of a row, at most
 template <int NCH>
 constexpr int queue_rows() { return 12; }
@@ -990,7 +994,7 @@ int bevpool_launch_forward(const void *P, const void *F, const bevpool_plan_s *p
     const bool maxr = reduce == BEVPOOL_MAX;
     hipEvent_t fstop = combine ? nullptr : stop;
     const bool seg = a.n_planes > 1;   // some combos split into row segments
-    // the queue: no gathered cells, and every column item resident at once
+    // the queue: no gathered cells, and LDS for every column item at once
     constexpr int kCus = 256;
     const bool queued = seg && plan->n_generic == 0 && nch <= kQueueChunks &&
                         int64_t(a.n_items) * batch * n_slices <= int64_t(kCus) * queued_per_cu(nch);
