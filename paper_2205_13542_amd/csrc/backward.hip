@@ -32,7 +32,9 @@
 // kernel below: 56 us in the last two). 128 channels in one
 // launch read P once (236 bins x 64 x 176: 322 us in two launches of 80 and 48
 // channels, 165 us in one), with a dP product in two sums: one of 128 products
-// rounds worse, 2.0e-7 against 1.5e-7 from exact. Tried and no faster: 8 waves
+// rounds worse, 2.0e-7 against 1.5e-7 from exact. Four columns of 128 channels
+// spill 19 of the 256 registers at two waves per SIMD (two columns none, 173 us
+// there). Tried and no faster: 8 waves
 // per workgroup; three waves per SIMD with four columns, by spilling; the next
 // two columns' rows in flight; two columns' products interleaved.
 //

@@ -147,8 +147,8 @@ constexpr int kOnePlane = 0, kStored = 1, kQueued = 2;
 // 126 us; 128 channels, 1-degree rig, 42 against 58 us). At fewer channels the LDS
 // holds more workgroups than the registers (19 to a CU at 16 channels), and the
 // queue is the faster form up to there, also where not all items are resident
-// (forward alone, 1-degree rig, fp32, stored against queued: 16 channels, one
-// frame 32 / 26 us, four 66 / 52; 48 channels, one frame 37 / 31).
+// (forward alone, 1-degree rig, fp32, before there was a queue and with it: 16
+// channels, one frame 32 and 26 us, four 66 and 52; 48 channels 37 and 31).
 constexpr int kQueueChunks = 5;    // 16-channel chunks of a row, at most
 template <int NCH>
 constexpr int queue_rows() { return 12; }
